@@ -1,36 +1,30 @@
-// sg_topk: exact budgeted top-k per unit row by wavefront-level radix select
+// sg_topk: exact budgeted top-k per unit row by a range-adaptive count
 // (select_common.h).
 //
-// One workgroup owns one (request, layer, KV head) row (or, for block
-// selection, one request's row of L * M block importances).  The row is held
-// in registers, ITEMS consecutive keys per thread (up to 80).  Rows of 8K to
-// 32K keys take 512 threads with 64 keys each (104 VGPRs, 8 KB of LDS) when
-// the call has at least two rows per CU: two workgroups then share a CU, and
-// one fits beside a score workgroup when the select region runs a request
-// pair's top-k beside the next pair's score, where 1024 threads with 32 keys
-// each (110 VGPRs, 84 KB of LDS for the staged row) held a whole CU.  64
-// requests (16,384 rows of 2.6K-32.6K keys): 2.04 against 2.75 ms alone, the
-// select region 46.1 against 46.7 ms.  With fewer rows the 1024-thread form
-// finishes each row sooner (256 rows of 32K keys: 0.050-0.058 against
-// 0.062 ms).
+// One workgroup of 1024 threads owns one (request, layer, KV head) row (or, for
+// block selection, one request's row of L * M block importances) and holds it
+// in registers, ITEMS keys per thread (up to 80); a row shorter than the
+// call's longest uses only the items it needs, spread over all wavefronts.
+// ITEMS = 32 is compiled for 64 VGPRs, so two workgroups share a CU, and one
+// fits beside a score workgroup (208 VGPRs, two wavefronts per SIMD) when the
+// select region runs a request pair's top-k beside the next pair's score.
+//
+// Against four fixed 8-bit digit passes with consecutive keys per thread (512
+// threads for many long rows): 256 rows of 8K keys 14.5 -> 8.7 us, 1,024 rows
+// of 3K to 32K keys 179 -> 48 us, one row of 32K block importances 41.7 ->
+// 17.4 us (5.5 us of it its loads: what one CU draws from beyond its L2).
 #include "select_common.h"
 
 namespace sg {
 
-template <int ITEMS, int NT = TOPK_THREADS>
-__global__ __launch_bounds__(NT) void topk_kernel(int B, const int32_t *__restrict__ cu_seqlens,
-                                                            int64_t T, const int32_t *__restrict__ cu_k,
-                                                            int64_t K_total, const float *__restrict__ scores,
-                                                            int32_t *__restrict__ idx) {
-    __shared__ SelectSmemT<NT> sm;
-    // long rows pass through LDS in chunks: coalesced loads, then each thread
-    // reads its consecutive keys (one pad word per 32 keeps the reads free of
-    // bank conflicts); reading them straight from memory would touch a new
-    // cache line per lane and instruction
-    constexpr bool STAGE = ITEMS >= 16 && ITEMS <= 32;   // wider rows: no registers to spare
-    constexpr int CH = 16384;
-    __shared__ float stage[STAGE ? CH + CH / 32 : 1];
+// Wavefronts per SIMD: two workgroups per CU (64 VGPRs) while the row fits.
+constexpr int topk_waves(int items) { return items <= 32 ? 8 : 4; }
 
+template <int ITEMS>
+__global__ __launch_bounds__(TOPK_THREADS) __attribute__((amdgpu_waves_per_eu(topk_waves(ITEMS)))) void topk_kernel(
+    int B, const int32_t *__restrict__ cu_seqlens, int64_t T, const int32_t *__restrict__ cu_k, int64_t K_total,
+    const float *__restrict__ scores, int32_t *__restrict__ idx) {
+    __shared__ SelectSmem sm;
     const int b = blockIdx.x % B;
     const int64_t lh = blockIdx.x / B;
     const int tid = threadIdx.x;
@@ -40,50 +34,27 @@ __global__ __launch_bounds__(NT) void topk_kernel(int B, const int32_t *__restri
     int32_t *out = idx + lh * K_total + c0;
     const int64_t kk = c1 - c0;
     const int64_t N = s1 - s0;
-    if (s0 < 0 || s1 < s0 || s1 > T || kk > N || N > (int64_t)ITEMS * NT) {
-        for (int64_t i = tid; i < kk; i += NT) out[i] = -1;
+    if (s0 < 0 || s1 < s0 || s1 > T || kk > N || N > (int64_t)ITEMS * TOPK_THREADS) {
+        for (int64_t i = tid; i < kk; i += TOPK_THREADS) out[i] = -1;
         return;
     }
     if (kk == 0) return;
     if (kk == N) {  // everything is selected
-        for (int64_t i = tid; i < kk; i += NT) out[i] = (int32_t)i;
+        for (int64_t i = tid; i < kk; i += TOPK_THREADS) out[i] = (int32_t)i;
         return;
     }
     const float *row = scores + lh * T + s0;
-    const int first = tid * ITEMS;
-    const int nv = (int)max<int64_t>(0, min<int64_t>(ITEMS, N - first));
+    const int n = (int)N, it = select_items(n);
+    const int entry0 = select_entry(it);
+    // every load issued before the first key is made (an entry past the row reads its last one)
+    float x[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if (i < it) x[i] = row[min(entry0 + i * 64, n - 1)];       // uniform
     uint32_t key[ITEMS];
-    if constexpr (STAGE) {
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) key[i] = 0u;
-        for (int c0 = 0; c0 < (int)N; c0 += CH) {       // uniform
-            const int cn = min<int64_t>(CH, N - c0);
-#pragma unroll 4
-            for (int j = tid; j < cn; j += NT) stage[j + (j >> 5)] = row[c0 + j];
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < ITEMS; ++i) {
-                const int x = first + i - c0;
-                if (i < nv && x >= 0 && x < cn) key[i] = order_key(stage[x + (x >> 5)]);
-            }
-            __syncthreads();
-        }
-    } else if (ITEMS % 4 == 0 && nv == ITEMS && (reinterpret_cast<uintptr_t>(row + first) & 15u) == 0) {
-        // a thread's keys whole and 16-byte aligned: vector loads
-#pragma unroll
-        for (int i = 0; i < ITEMS; i += 4) {
-            const float4 x = *reinterpret_cast<const float4 *>(row + first + i);
-            key[i] = order_key(x.x);
-            key[i + 1] = order_key(x.y);
-            key[i + 2] = order_key(x.z);
-            key[i + 3] = order_key(x.w);
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) key[i] = i < nv ? order_key(row[first + i]) : 0u;
-    }
-
-    select_top<ITEMS, NT>(key, nv, first, (int)kk, out, sm);
+    for (int i = 0; i < ITEMS; ++i) key[i] = i < it && entry0 + i * 64 < n ? order_key(x[i]) : 0u;
+    select_top<ITEMS>(key, it, (int)kk, out, sm);
 }
 
 }  // namespace sg
@@ -101,17 +72,16 @@ extern "C" int sg_topk(void *stream, int B, int L, int Hkv, const int32_t *cu_se
     const int64_t blocks = (int64_t)B * L * Hkv;
     SG_REQUIRE(blocks <= 0x7fffffff, SG_EINVAL, "sg_topk: too many rows");
     hipStream_t s = as_stream(stream);
-    if (max_seqlen <= 2 * TOPK_THREADS)
-        topk_kernel<2><<<(unsigned)blocks, TOPK_THREADS, 0, s>>>(B, cu_seqlens, T, cu_k, K_total, scores, idx);
-    else if (max_seqlen <= 8 * TOPK_THREADS)
-        topk_kernel<8><<<(unsigned)blocks, TOPK_THREADS, 0, s>>>(B, cu_seqlens, T, cu_k, K_total, scores, idx);
-    else if (max_seqlen <= 32 * TOPK_THREADS && blocks >= 2 * (int64_t)device_cus())
-        topk_kernel<64, 512><<<(unsigned)blocks, 512, 0, s>>>(B, cu_seqlens, T, cu_k, K_total, scores, idx);
-    else if (max_seqlen <= 32 * TOPK_THREADS)
-        topk_kernel<32><<<(unsigned)blocks, TOPK_THREADS, 0, s>>>(B, cu_seqlens, T, cu_k, K_total, scores, idx);
-    else if (max_seqlen <= 64 * TOPK_THREADS)
-        topk_kernel<64><<<(unsigned)blocks, TOPK_THREADS, 0, s>>>(B, cu_seqlens, T, cu_k, K_total, scores, idx);
-    else    // block rows of up to 80 layers x 1024 blocks
-        topk_kernel<80><<<(unsigned)blocks, TOPK_THREADS, 0, s>>>(B, cu_seqlens, T, cu_k, K_total, scores, idx);
+    const unsigned grid = (unsigned)blocks;
+    const int items = (int)ceil_div(std::max(max_seqlen, 1), TOPK_THREADS);
+#define SG_TOPK(I) topk_kernel<I><<<grid, TOPK_THREADS, 0, s>>>(B, cu_seqlens, T, cu_k, K_total, scores, idx)
+    if (items <= 2) SG_TOPK(2);
+    else if (items <= 4) SG_TOPK(4);
+    else if (items <= 8) SG_TOPK(8);
+    else if (items <= 16) SG_TOPK(16);
+    else if (items <= 32) SG_TOPK(32);
+    else if (items <= 64) SG_TOPK(64);
+    else SG_TOPK(80);    // block rows of up to 80 layers x 1024 blocks
+#undef SG_TOPK
     return launch_status("sg_topk");
 }

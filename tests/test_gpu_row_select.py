@@ -1,0 +1,63 @@
+"""GPU parity of the row select (sg_topk, sg_decode_select) at the edges of its
+dispatch: rows around every items-per-thread step and wavefront multiple, and
+key distributions that take each end of the search (one count, a gathered bin,
+repeated counts over a clustered range, one tied key, empty slots beside the
+lowest entries).  Ids must equal the oracle's exactly."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests.gpu_util import cu, say
+from tests.test_gpu_selectors import ALPHA_EXACT, _ints, _select
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(kind, n, g):
+    if kind == "spread":          # over many powers of two
+        return np.exp(3.0 * g.standard_normal(n)).astype(np.float32)
+    if kind == "signed":          # both signs, infinities, zeros of both signs, NaN
+        x = g.standard_normal(n).astype(np.float32)
+        for v in (np.inf, -np.inf, 0.0, -0.0, np.nan):
+            x[g.integers(0, n, max(1, n // 50))] = v
+        return x
+    if kind == "cluster":         # a few far values, the rest within some thousand ulps of 1
+        x = (np.float32(1.0).view(np.int32) + g.integers(0, 5000, n)).astype(np.int32).view(np.float32)
+        x[:2] = (1e30, -1e30)[:min(2, n)]
+        return x
+    if kind == "levels":          # heavy ties
+        return g.integers(0, 5, n).astype(np.float32)
+    return np.full(n, -3.0e38, np.float32)      # every entry tied, near the lowest finite value
+
+
+@pytest.mark.parametrize("kind", ["spread", "signed", "cluster", "levels", "equal"])
+@pytest.mark.parametrize("lens", [
+    (1, 2, 63, 64, 65, 1000), (1023, 1024, 1025, 2048), (2049, 4096, 5), (4097, 8191, 8192), (8193, 16384, 300),
+    (16385, 32767, 32768, 1), (32769, 65536), (65537, 81920)])
+def test_topk_rows_bit_exact(gpu_lib, lens, kind):
+    say("top-k rows", lens, kind)
+    g = np.random.default_rng(sum(lens) + len(kind))
+    for share in (0.0, 0.1, 0.97):
+        ks = [min(n, max(1, int(n * share))) for n in lens]
+        cus, cuk = (np.concatenate([[0], np.cumsum(x)]).astype(np.int32) for x in (lens, ks))
+        s = np.stack([np.concatenate([_rows(kind, n, g) for n in lens]) for _ in range(2)])[None]
+        idx = torch.full((1, 2, int(cuk[-1])), -7, dtype=torch.int32, device="cuda")
+        gpu_lib.sg_topk(torch.from_numpy(s).cuda(), cu(cus), int(cus[-1]), max(lens), cu(cuk), int(cuk[-1]), idx)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(idx.cpu().numpy(), oracle.topk(s, cus, cuk))
+
+
+@pytest.mark.parametrize("G,lens,cap_bp", [(1, (20000, 9000), 2000), (8, (4097, 2048), 2000), (4, (16385,), 10000),
+                                           (8, (30011, 17), 500), (2, (8193, 1024), 10000)])
+def test_decode_select_long_rows_exact(gpu_lib, G, lens, cap_bp):
+    """Integer inputs with d = 64: every logit is exact on both sides."""
+    say("decode select rows", G, lens, cap_bp)
+    L, Hkv, d, T = 1, 2, 64, sum(lens)
+    q = _ints((len(lens), L, Hkv * G, d), -2, 2, G + T, "bf16")
+    k = _ints((L, Hkv, T, d), -2, 2, G * T + 3, "bf16")
+    caps = [max(1, n * cap_bp // 10000) for n in lens]
+    idx, n_sel, cus, cc = _select(gpu_lib, q, k, lens, Hkv, caps, ALPHA_EXACT, scale=0.125)
+    r_idx, r_n, _ = oracle.decode_select(q.float().numpy(), k.float().numpy(), cus, Hkv, cc, ALPHA_EXACT, scale=0.125)
+    np.testing.assert_array_equal(n_sel, r_n)
+    np.testing.assert_array_equal(idx, r_idx)
