@@ -7,67 +7,71 @@
 // tied with the k-th largest are all picked.  counts[j] is the number of
 // (q head, window row) pairs of the unit that pick key j.
 //
-// The k-th largest logit of every row is found exactly by a radix select,
-// most significant digit first, over the logits' bit patterns.  A float maps
-// to an unsigned key of the same order (sign bit set for non-negative values,
-// every bit flipped for negative ones); each pass resolves one digit of DB
-// bits of every row's threshold key:
+// The k-th largest logit of every row is found exactly, in three passes over
+// the logits (recomputed by the MFMA engine of sg_score each time) and a small
+// sample:
 //
-//   hist  : recompute the logits with the MFMA engine of sg_score in the
-//           C = K Q^T layout (a lane's values of a block belong to one row)
-//           and, for each value whose key matches its row's resolved prefix,
-//           add one to the row's bin of the next digit (LDS atomics, bins x
-//           rows); the chunk's nonzero bins go into the unit's global
-//           histogram with global atomics (integer adds: the result does not
-//           depend on their order);
-//   digit : per row, walk the bins from the top until the remaining rank is
-//           reached: that bin's digit extends the prefix, the rank drops by
-//           the keys above the bin, and the bins are cleared for the next
-//           pass.
+//   sample : the logits of 512 to 2048 keys spread over the prompt (held in
+//            registers) give each row an interval [a, b) that holds its k-th
+//            largest logit with near certainty: the sample's quantiles 4.75
+//            standard deviations around the wanted rank;
+//   hist   : every logit of the row goes to one of 64 equal bins of [a, b), or
+//            below or above it (LDS atomics, bins x rows); the chunk's bins go
+//            into the unit's global histogram with integer atomics;
+//   digit  : one thread per row finds the bin of the k-th largest and the
+//            smallest and largest float in it;
+//   again  : units with a row that the sample misjudged or whose bin holds more
+//            than TS_CMAX keys take hist and digit once more, over the next
+//            interval or that bin (every other unit returns at once);
+//   gather : the values inside a row's bin (a few tens at most) are appended
+//            to the row's list, in LDS, then in the workspace;
+//   pick   : the exact k-th largest among them is the row's threshold;
+//   radix  : rows still unresolved (ties, NaN) take an exact radix select over
+//            the logits' bit patterns, one workgroup per 32 rows with such a
+//            row (every other one returns at once);
+//   count  : each key's picks, counted against the rows' thresholds.
 //
-// After 32 bits the prefix is the key of the row's k-th largest value.  Two
-// shortcuts end most rows much earlier:
-//   settle : a row whose chosen bin holds exactly the keys it still needs is
-//            done (every key at or above the bin's lower edge is picked and
-//            nothing below it);
-//   gather : once 18 bits are resolved a row's bin holds only a few keys
-//            (with real-valued logits); a row whose bin holds at most TS_CMAX
-//            keys gathers their values (one more logit pass appends each to
-//            the row's list, in LDS, then in the workspace) and a small kernel
-//            picks the exact k-th largest among them.  Rows with larger bins
-//            (many ties) keep the radix passes.
-// A unit with no row left to resolve returns at the start of the remaining
-// passes.  The count pass recomputes the logits in the same layout, so each
-// row compares exactly the values its threshold came from (the same MFMA
-// operands in the same order), and counts each key's picks with one wavefront
-// ballot per value (one bit per row) and population counts.
+// Against a radix select in 6-bit digits for all rows (three histogram passes,
+// gather and count, one workgroup per CU in each): 32 layers x 8 heads of 8K
+// keys, 256 rows each, at 20%: 1.14 -> 0.62-0.65 ms (sample 62, hist 187, digit
+// 13, gather 190, pick 25, count 137 us, the three idle launches 14 us); one
+// unit in ten or so has a row that takes hist again.  Rows of nothing but ties
+// (every logit one of a few values) are slower: they reach the radix select.
 //
-// The passes work on the raw products q . k_j: the positive scale 1/sqrt(d)
-// keeps their order.  The picks compare floats against the threshold: the
-// row's k-th largest value, or a settled bin's lower edge (the float of the
-// smallest key in the bin's range, -inf below the keys of -inf), which picks
-// exactly the keys at or above the edge.  -0 sorts just below +0 as a key; as
-// floats they are equal and picked together, as for any other tie, so a bin
-// whose lower edge is +0 does not settle early (-0 would tie it).
+// A logit's bits are the same in every pass: the same MFMA operands in the
+// same contraction order (C = K Q^T in hist and gather, Q K^T in count).  The
+// passes work on the raw products q . k_j: the positive scale 1/sqrt(d) keeps
+// their order.  Bins are a monotone function of the logit, so the bin's
+// bounds are exact floats.  Values order as their bit patterns do: a NaN with
+// the sign bit set below -inf, any other above +inf; -0 and +0 are equal
+// floats and picked together.
 #include <algorithm>
 
 #include "score_tiles.h"
 
 namespace sg {
 
-constexpr int TS_MAXBINS = 64;     // bins per row of the global histogram (digits of at most 6 bits)
-constexpr int TS_MAXPASS = 8;      // per-unit flag words per call (7 passes at most)
-constexpr int TS_CMAX = 32;        // keys a row may gather
-constexpr int TS_GATHER_BITS = 18; // resolved bits before a row may gather
-constexpr uint32_t TS_GATHER = 0x80000000u;   // need flag: the row gathers its bin
+constexpr int TS_BINS = 64;        // bins of a row's interval
+constexpr int TS_CMAX = 92;        // keys a row may gather
+constexpr int TS_LIST = 32;        // of them from one chunk
+constexpr int TS_ROW_WORDS = 99;   // workspace words per row: six below, the rest bins, then lists
+constexpr int TS_UNIT_WORDS = 9;
+static_assert(6 + TS_CMAX <= TS_ROW_WORDS && TS_BINS <= TS_CMAX, "the row lists take the bins' place");
 
-// Digit width: 6 bits (at most 6 histogram passes) while the bins of up to
-// 256 rows fit in LDS beside the two K tiles; 5 bits (at most 7) for 512 rows.
-template <int NW>
-struct TsDigits {
-    static constexpr int DB = NW == 8 ? 5 : 6;
-    static constexpr int NB = 1 << DB;
+// The call's workspace.
+struct TsWork {
+    float *xa, *xb;        // [rows] interval scale and offset, then the bounds of the row's bin
+    uint32_t *need;        // [rows] rank inside the bin | keys in the bin << 16; 0: settled; TS_AGAIN; TS_RADIX
+    uint32_t *above;       // [rows] keys above the interval
+    uint32_t *gcount;      // [rows] keys gathered
+    float *thr;            // [rows] threshold
+    uint32_t *hist;        // [units][TS_BINS][R] bins
+    uint32_t *list;        // [rows][TS_CMAX] gathered values (in the bins' place)
+    uint32_t *fail;        // [units] bit per 32 rows: a row needs the radix select
+    uint32_t *again;       // [units] a row of the unit needs another histogram
 };
+constexpr uint32_t TS_AGAIN = 0xffffffffu;      // need: another histogram over the interval in xa, xb
+constexpr uint32_t TS_RADIX = 0xfffffffeu;      // need: the radix select, between xa and xb (NaN: anywhere)
 
 __device__ __forceinline__ uint32_t order_key(float f) {
     const uint32_t x = __float_as_uint(f);
@@ -84,50 +88,281 @@ __device__ __forceinline__ float threshold_value(uint32_t key) {
     return key < NEG_INF_KEY ? -INFINITY : key_value(key);
 }
 
-// One block of the histogram pass.  FIRST: the first digit, every value
-// counts.  Later passes: c = prefix ^ (the sign flip of the prefix's sign), so
-// for a value x of the prefix's sign, x ^ c = key(x) ^ prefix, whose bits
-// above the digit are zero exactly when the key matches the prefix; a value of
-// the other sign sets the top bit (the prefix always covers the sign bit).
-template <typename T, int D, int NW, bool FIRST, bool MASK>
+// The bin of logit x: with t = x * scale + offset, t in [1, 2) over the row's
+// interval, the exponent and the top six mantissa bits of t count up through
+// the interval's 64 bins (TS_LOW + 1 .. TS_LOW + 64); below it (negative t
+// too) TS_LOW, above it TS_LOW + 65.  Signed compares put every bit pattern,
+// NaN included, where its order is.
+constexpr int TS_LOW = (0x3f800000 >> 17) - 1;
+__device__ __forceinline__ int ts_bin(float x, float scale, float off) {
+    const int b = (int)__float_as_uint(fmaf(x, scale, off)) >> 17;
+    return min(max(b, TS_LOW), TS_LOW + TS_BINS + 1);
+}
+
+// The number of low bits that hold every set bit of the lanes' x.
+__device__ __forceinline__ int wave_max_bits(uint32_t x) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) x |= (uint32_t)__shfl_xor((int)x, o, 64);
+    return 32 - __builtin_clz(x | 1u) - (x == 0u ? 1 : 0);
+}
+
+// The rank (from the top) of the wanted key among the n a row sees.
+__device__ __forceinline__ int64_t ts_rank(int64_t n, int ratio_bp) {
+    return min(max(n, (int64_t)1), max((int64_t)1, n * ratio_bp / 10000));
+}
+
+// ---------------------------------------------------------------- sample
+
+// One workgroup of NWV wavefronts per (unit, ROWS rows): wavefront w holds the
+// logits of SPW sampled keys for those rows in registers, C = K Q^T, keys and
+// queries straight from memory.  The rows' intervals are narrowed by counting
+// the sample in 64 bins of the current interval (first [min, max]) and moving
+// its ends to the bins of the bounding ranks, again (up to four times) while
+// some row's interval holds many more samples than the ranks ask for (far
+// outliers; the larger sample always twice).  Also clears the unit's counters.
+template <typename T, int D, int NWV, int ROWS>
+__global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) void ts_sample_kernel(
+    int B, int L, int Hq, int Hkv, int W, const int32_t *__restrict__ cu_seqlens, int64_t T_,
+    const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int ratio_bp, TsWork ws) {
+    using M = MT<T, D>;
+    constexpr int NRB = ROWS / M::BM, SPW = 8192 / ROWS, NKB = SPW / M::BM, NS = SPW * NWV;
+    constexpr int SB = 128, QB = SB / 4;       // bins of the sample; a quarter of them
+    __shared__ uint32_t bins[SB + 1][ROWS];
+    __shared__ float smin[NWV][ROWS], smax[NWV][ROWS], ra[ROWS], rs[ROWS];
+    __shared__ int qsum[4][ROWS], found[4][ROWS];  // found: the bins of the two ranks and the samples above them
+    const int R = (Hq / Hkv) * W, ngrp = (int)ceil_div(R, ROWS);
+    const int64_t u = blockIdx.x / ngrp;
+    const int grp = blockIdx.x % ngrp;
+    const UnitGeom g = unit_geom(u, B, Hkv, cu_seqlens, T_);
+    const int N = (int)g.N, tid = threadIdx.x, lane = tid % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    // the rows' counters
+    for (int i = tid; i < TS_BINS * ROWS; i += 64 * NWV) {
+        const int row = grp * ROWS + i % ROWS;
+        if (row < R) ws.hist[(u * TS_BINS + i / ROWS) * R + row] = 0u;
+    }
+    const int myrow = grp * ROWS + tid;        // threads 0 .. ROWS - 1: a row each
+    const bool owner = tid < ROWS && myrow < R;
+    if (owner) {
+        ws.above[u * R + myrow] = 0u;
+        ws.gcount[u * R + myrow] = 0u;
+        if (myrow == 0) ws.fail[u] = ws.again[u] = 0u;
+    }
+    if (N < W) return;                         // uniform: the count pass writes zeros
+    const T *qunit = q_win + (((int64_t)g.b * L + g.l) * Hq + (int64_t)g.h * (Hq / Hkv)) * W * D;
+    const T *kunit = k + ((int64_t)g.l * k_layer_rows + (int64_t)g.h * T_ + g.s0) * D;
+    // sampled key i of ns: spread over the keys every row sees
+    // (one in eight, at least 512: a short prompt beside long ones leaves
+    // wavefronts without keys, which only keep the barriers)
+    const int seen = N - W + 1, ns = min(seen, max(512, min(NS, seen / 8 / SPW * SPW))), stride = seen / ns;
+    const bool busy = wave * SPW < ns;         // uniform across the wavefront
+    TA<T, D> qf[NRB][M::KS];
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+        const T *p = qunit + (int64_t)min(grp * ROWS + rb * M::BM + lane % M::BM, R - 1) * D;
+#pragma unroll
+        for (int ks = 0; ks < M::KS; ++ks) qf[rb][ks] = M::load_global(p, ks, lane);
+    }
+    TC<T, D> val[NKB][NRB];
+    if (busy) {
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+            const int i = wave * SPW + kb * M::BM + lane % M::BM;
+            const T *p = kunit + (int64_t)(min(i, ns - 1) * (int64_t)stride + stride / 2) * D;
+            TA<T, D> kf[M::KS];
+#pragma unroll
+            for (int ks = 0; ks < M::KS; ++ks) kf[ks] = M::load_global(p, ks, lane);
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) val[kb][rb] = block_mma<T, D, true>(kf, qf[rb]);
+        }
+    }
+    // a short prompt's values past the sample become NaN, which every compare
+    // and minimum below leaves out
+    if (busy && ns % SPW != 0) {               // uniform
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+            for (int v = 0; v < M::NV; ++v) {
+                const bool live = wave * SPW + kb * M::BM + M::crow(v, lane) < ns;
+#pragma unroll
+                for (int rb = 0; rb < NRB; ++rb) val[kb][rb][v] = live ? val[kb][rb][v] : __builtin_nanf("");
+            }
+    }
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+        float mn = INFINITY, mx = -INFINITY;
+        if (busy) {
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                for (int v = 0; v < M::NV; ++v) {
+                    mn = fminf(mn, val[kb][rb][v]);
+                    mx = fmaxf(mx, val[kb][rb][v]);
+                }
+        }
+#pragma unroll
+        for (int off = M::BM; off < 64; off <<= 1) {
+            mn = fminf(mn, __shfl_xor(mn, off, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+        }
+        if (lane < M::BM) {
+            smin[wave][rb * M::BM + lane] = mn;
+            smax[wave][rb * M::BM + lane] = mx;
+        }
+    }
+    __syncthreads();
+    // a row's interval [a, b] and the sample ranks (from the top) that bound it
+    // (thread t: row t % ROWS)
+    const int col = tid % ROWS, quarter = tid / ROWS % 4;
+    const bool scans = tid < 4 * ROWS;
+    float a = smin[0][col], b = smax[0][col];
+    for (int w = 1; w < NWV; ++w) {
+        a = fminf(a, smin[w][col]);
+        b = fmaxf(b, smax[w][col]);
+    }
+    const float top = b;
+    const int64_t nrow = seen + (grp * ROWS + col) % W;
+    const float p = (float)ts_rank(nrow, ratio_bp) / (float)nrow, r = p * ns;
+    // five standard deviations less a little; near the ends the wanted key lies inside the
+    // sample's extremes unless all `r` expected samples beyond it are missing
+    // (e^-11 from r = 11 on), else the interval is open there (r_hi < 0, r_lo > ns)
+    const float spread = 4.75f * sqrtf(r * (1.f - p)) + 1.f;
+    const int r_hi = max((int)floorf(r - spread), r >= 11.f ? 0 : -1);
+    const int r_lo = min((int)ceilf(r + spread), (float)ns - r >= 11.f ? ns : ns + 1);
+    for (int round = 0; round < 4; ++round) {
+        const float sc = b > a ? (float)SB / (b - a) : 0.f;
+        if (tid < ROWS) {
+            ra[tid] = a;
+            rs[tid] = sc;
+            found[0][tid] = SB - 1;                    // ranks above or below every bin: keep that end
+            found[1][tid] = 0;
+            found[2][tid] = found[3][tid] = 0;
+        }
+        for (int i = tid; i < (SB + 1) * ROWS; i += 64 * NWV) (&bins[0][0])[i] = 0u;
+        __syncthreads();
+        if (busy) {
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) {
+                const int row = rb * M::BM + lane % M::BM;
+                const float lo = ra[row], rsc = rs[row];
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                    for (int v = 0; v < M::NV; ++v) {
+                        const float x = val[kb][rb][v];
+                        // bin SB: above the interval (its upper end too, after the first round)
+                        const int d = min((int)((x - lo) * rsc), round == 0 ? SB - 1 : SB);
+                        if (x >= lo) atomicAdd(&bins[max(d, 0)][row], 1u);
+                    }
+            }
+        }
+        __syncthreads();
+        // four threads per row scan a quarter of its bins each, from the top
+        uint32_t c[QB];
+        int sum = 0;
+        if (scans) {
+#pragma unroll
+            for (int j = 0; j < QB; ++j) {
+                c[j] = bins[(4 - quarter) * QB - 1 - j][col];
+                sum += (int)c[j];
+            }
+            qsum[quarter][col] = sum;
+        }
+        __syncthreads();
+        if (scans) {
+            int cum = (int)bins[SB][col];
+            for (int w = 0; w < quarter; ++w) cum += qsum[w][col];
+#pragma unroll
+            for (int j = 0; j < QB; ++j) {
+                const int d = (4 - quarter) * QB - 1 - j, next = cum + (int)c[j];
+                if (cum <= r_hi && next > r_hi) {      // the first sample past the upper rank
+                    found[0][col] = d;
+                    found[2][col] = cum;
+                }
+                if (cum < r_lo && (next >= r_lo || d == 0)) {      // down to the bin of the lower rank
+                    found[1][col] = d;
+                    found[3][col] = next;
+                }
+                cum = next;
+            }
+        }
+        __syncthreads();
+        const int hi_bin = found[0][col], lo_bin = found[1][col];
+        const float step = (b - a) / (float)SB;
+        const float na = a + lo_bin * step, nb = hi_bin == SB - 1 ? b : a + (hi_bin + 1) * step;
+        if (nb > na) {
+            a = na;
+            b = nb;
+        }
+        const int want = min(r_lo, ns) - max(r_hi, 0);
+        const int wide = grp * ROWS + col < R && found[3][col] - found[2][col] > want + want / 2 + 8;
+        if (__syncthreads_or(wide) == 0 && round >= (NS > 512 ? 1 : 0)) break;     // uniform
+    }
+    if (owner) {
+        // open ends: room beyond the sample's extremes
+        if (r_hi < 0) b = top + 4.f * (top - a);
+        else if (b >= top) b = top + 1e-3f * (top - a);
+        if (r_lo > ns) a -= b - a;
+        if (!(b > a)) {                        // a constant sample
+            const float e = fmaxf(fabsf(a) * 1e-5f, 1e-20f);
+            a -= e;
+            b += e;
+        }
+        const float scale = 1.f / (b - a), off = 1.f - a * scale;
+        const bool ok = b > a && scale < INFINITY && scale > 0.f && fabsf(off) < INFINITY;
+        ws.xa[u * R + myrow] = ok ? scale : 0.f;           // 0, 0: every logit below the interval
+        ws.xb[u * R + myrow] = ok ? off : 0.f;
+    }
+}
+
+// ---------------------------------------------------------------- hist
+
+// Keys per LDS tile of the hist and gather passes: 64-key tiles leave room for
+// two workgroups per CU beside the bins or the lists.
+template <typename T>
+constexpr int ts_tile_keys() { return 64; }
+
+// One block of the histogram pass.  A word of the bins holds two rows' counts
+// (row blocks 2 i and 2 i + 1 of the wavefront, one after the other in a lane,
+// so they never meet in one instruction); a chunk's counts stay below 2^16.
+// No branch per value (it would split the block and undo the MFMA / vector
+// interleave): values outside the interval go to the end bins.
+template <typename T, int D, int NW, bool MASK>
 struct HistStep {
-    static constexpr int NRB = QFrags<T, D>::NRB;
-    uint32_t *hist;                 // LDS [bins][64 * NW]
-    const uint32_t (&c)[NRB];
+    using M = MT<T, D>;
+    static constexpr int NRB = QFrags<T, D>::NRB, WORDS = 32 * NW;
+    uint32_t *hist;                 // LDS [TS_BINS + 2][WORDS]
+    const float (&scale)[NRB], (&off)[NRB];
     const int (&pos)[NRB];          // window position of the lane's row (-1: padded row)
-    int lane, wave, key0, sh;
-    uint32_t lim;                   // bins of this pass (bin lim takes the values that do not count)
+    int lane, wave, key0;
     __device__ __forceinline__ void operator()(TC<T, D> &acc, int kb, int rb) const {
-        using M = MT<T, D>;
-        uint32_t *h = hist + wave * 64 + rb * M::BM + lane % M::BM;      // bin 0 of the lane's row
-        // no branch per value (it would split the block and undo the MFMA /
-        // vector interleave): a value that does not count goes to bin lim,
-        // which is never read
+        uint32_t *h = hist + wave * 32 + (rb / 2) * M::BM + lane % M::BM - TS_LOW * WORDS;
+        const uint32_t one = rb % 2 ? 0x10000u : 1u;
 #pragma unroll
         for (int v = 0; v < M::NV; ++v) {
-            uint32_t t = FIRST ? order_key(acc[v]) >> sh : min((__float_as_uint(acc[v]) ^ c[rb]) >> sh, lim);
-            if (MASK) t = key0 + kb * M::BM + M::crow(v, lane) <= pos[rb] ? t : lim;
-            __hip_atomic_fetch_add(h + t * (64 * NW), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            int t = ts_bin(acc[v], scale[rb], off[rb]);
+            if (MASK) t = key0 + kb * M::BM + M::crow(v, lane) <= pos[rb] ? t : TS_LOW;
+            __hip_atomic_fetch_add(h + t * WORDS, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     }
 };
 
-template <typename T, int D, int NW, bool FIRST>
+template <typename T, int D, int NW, bool AGAIN>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void ts_hist_kernel(
     int B, int L, int Hq, int Hkv, int W, const int32_t *__restrict__ cu_seqlens, int64_t T_,
     const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int nchunk, int chunk_keys,
-    int sh, int width, const uint32_t *__restrict__ busy, const uint32_t *__restrict__ pre,
-    uint32_t *__restrict__ ghist) {
+    TsWork ws) {
     using M = MT<T, D>;
-    using KT = KTile<T, D>;
-    constexpr int NRB = QFrags<T, D>::NRB, ROWS = 64 * NW, NB = TsDigits<NW>::NB;
+    constexpr int TKEYS = ts_tile_keys<T>();
+    using KT = KTile<T, D, TKEYS>;
+    constexpr int NRB = QFrags<T, D>::NRB, WORDS = 32 * NW;
     __shared__ __attribute__((aligned(16))) char kbA[KT::BYTES];
     __shared__ __attribute__((aligned(16))) char kbB[KT::BYTES];
-    __shared__ __attribute__((aligned(16))) uint32_t hist[(NB + 1) * ROWS];
+    __shared__ __attribute__((aligned(16))) uint32_t hist[(TS_BINS + 2) * WORDS];
     int64_t u;
     int chunk;
     unit_chunk((int64_t)L * Hkv * B, nchunk, u, chunk);
-    if (!FIRST && busy[u] == 0u) return;        // every row of the unit has settled
+    if (AGAIN && ws.again[u] == 0u) return;
     const UnitGeom g = unit_geom(u, B, Hkv, cu_seqlens, T_);
     const int G = Hq / Hkv, R = G * W;
     const int N = (int)g.N;
@@ -142,17 +377,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     KT::template load<NW>(kbA, kunit, key_begin, N, wave, lane);
     QFrags<T, D> q;
     q.load(qunit, R, wave, lane);
-    const int nbins = 1 << width;
-    for (int i = threadIdx.x; i < nbins * ROWS / 4; i += 64 * NW)
+    for (int i = threadIdx.x; i < (TS_BINS + 2) * WORDS / 4; i += 64 * NW)
         reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
-    uint32_t c[NRB];
+    float scale[NRB], off[NRB];
     int pos[NRB];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
         const int row = wave * 64 + rb * M::BM + lane % M::BM;
         pos[rb] = row < R ? N - W + row % W : -1;
-        const uint32_t p = (!FIRST && row < R) ? pre[u * R + row] : 0u;
-        c[rb] = p ^ ((p & 0x80000000u) ? 0x80000000u : 0xffffffffu);
+        const bool on = row < R && (!AGAIN || ws.need[u * R + row] == TS_AGAIN);
+        scale[rb] = on ? ws.xa[u * R + row] : 0.f;         // 0, 0: every logit below the interval
+        off[rb] = on ? ws.xb[u * R + row] : 0.f;
     }
     TC<T, D> zero[NRB];
 #pragma unroll
@@ -162,9 +397,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         barrier_after_loads();      // tile t landed (and the bins are clear); tile t - 1 done everywhere
         const int key0 = key_begin + t * KT::TK;
         if (t + 1 < ntile) KT::template load<NW>(nxt, kunit, key0 + KT::TK, N, wave, lane);
-        const HistStep<T, D, NW, FIRST, MASK> f{hist, c, pos, lane, wave, key0, sh, (uint32_t)nbins};
-        if (MASK) tile_sweep_plain<T, D, true>(cur, q, zero, lane, f);
-        else tile_sweep<T, D, true>(cur, q, zero, lane, f);
+        const HistStep<T, D, NW, MASK> f{hist, scale, off, pos, lane, wave, key0};
+        if (MASK) tile_sweep_plain<T, D, true, TKEYS>(cur, q, zero, lane, f);
+        else tile_sweep<T, D, true, TKEYS>(cur, q, zero, lane, f);
     };
     const int nfull = full_tiles(key_begin, ntile, KT::TK, N, W);
     int t = 0;
@@ -177,133 +412,152 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         else step(t, kbA, kbB, std::true_type{});
     }
     barrier_after_loads();      // every bin final, no load in flight
-    uint32_t *gh = ghist + u * NB * (int64_t)R;
-    for (int i = threadIdx.x; i < nbins * ROWS; i += 64 * NW) {
-        const int row = i % ROWS;
-        const uint32_t v = hist[i];
-        if (row < R && v != 0u)
-            __hip_atomic_fetch_add(gh + (int64_t)(i / ROWS) * R + row, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the interval's bins and the keys above it; those below are not needed
+    for (int i = threadIdx.x; i < (TS_BINS + 1) * WORDS; i += 64 * NW) {
+        const uint32_t both = hist[i + WORDS];
+        const int d = i / WORDS, x = i % WORDS;            // word x: wavefront x / 32
+        const int row0 = x / 32 * 64 + x % 32 / M::BM * 2 * M::BM + x % M::BM;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int row = row0 + half * M::BM;
+            const uint32_t v = half ? both >> 16 : both & 0xffffu;
+            uint32_t *dst = d < TS_BINS ? ws.hist + (u * TS_BINS + d) * R + row : ws.above + u * R + row;
+            if (row < R && v != 0u) __hip_atomic_fetch_add(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
 }
 
-// One thread per (unit, row): the start of the select.  need = k, the rank
-// (from the top) of the wanted key; prefix = 0; the unit's bins and its
-// per-pass flags cleared.
-__global__ __launch_bounds__(256) void ts_init_kernel(int64_t nrows, int R, int W, int B, int Hkv,
-                                                      const int32_t *__restrict__ cu_seqlens, int64_t T_,
-                                                      int ratio_bp, uint32_t *__restrict__ pre,
-                                                      uint32_t *__restrict__ need, uint32_t *__restrict__ ghist,
-                                                      int nb, uint32_t *__restrict__ busy, int64_t units,
-                                                      uint32_t *__restrict__ gcount, uint32_t *__restrict__ gflag) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= nrows) return;
-    const int64_t u = i / R;
-    const int r = (int)(i % R);
+constexpr int TS_DIGIT_THREADS = 64;
+
+// The order key of the smallest float (in bit-pattern order) that falls into
+// bin `d` of the interval or above it.
+__device__ __forceinline__ uint32_t ts_bound(int d, float scale, float off) {
+    uint32_t lo = 0x007fffffu, hi = 0xff800000u;       // order keys of -inf and +inf; +inf is above
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo) / 2u;
+        if (ts_bin(key_value(mid), scale, off) >= d) hi = mid;
+        else lo = mid + 1u;
+    }
+    return lo;
+}
+
+// One thread per row, one workgroup per unit: the bin of the row's k-th
+// largest logit.  The bins of a row are R words apart, so a wavefront's 64 rows
+// read each bin as one contiguous run; 32 bins are read before any is used.
+template <bool AGAIN>
+__global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W, int B, int Hkv,
+                                                                     const int32_t *__restrict__ cu_seqlens,
+                                                                     int64_t T_, int ratio_bp, TsWork ws) {
+    const int64_t u = blockIdx.x;
+    if (AGAIN && ws.again[u] == 0u) return;
+    const int r = (int)blockIdx.y * TS_DIGIT_THREADS + (int)threadIdx.x;
+    if (r >= R) return;
+    const int64_t i = u * R + r;
+    if (AGAIN && ws.need[i] != TS_AGAIN) return;
     const UnitGeom g = unit_geom(u, B, Hkv, cu_seqlens, T_);
     const int64_t n = g.N - W + r % W + 1;                 // keys the row sees
-    const int64_t kk = std::min<int64_t>(std::max<int64_t>(n, 1), std::max<int64_t>(1, n * ratio_bp / 10000));
-    pre[i] = 0u;
-    need[i] = (uint32_t)kk;
-    uint32_t *h = ghist + u * nb * (int64_t)R + r;
-    for (int b = 0; b < nb; ++b) h[(int64_t)b * R] = 0u;
-    gcount[i] = 0u;
-    if (r == 0) {
-        for (int k = 0; k < TS_MAXPASS; ++k) busy[k * units + u] = 0u;
-        gflag[u] = 0u;
-    }
-}
-
-// One thread per (unit, row): pick this pass's digit of the threshold key.
-// The bins of a row are R words apart, so a wavefront's 64 rows read each bin
-// as one contiguous run; eight bins are read before any is used.  need = 0
-// marks a settled row (its bins are only cleared).  busy_in: the flags the
-// previous pass set (a unit without one did not run this pass); busy_out: set
-// for the unit of every row that has not settled (NULL after the last digit).
-// gflag (the digit after which rows may gather, else NULL): a row whose bin
-// holds at most TS_CMAX keys is flagged to gather them (need | TS_GATHER) and
-// sets gflag of its unit instead of busy_out.
-__global__ __launch_bounds__(256) void ts_digit_kernel(int64_t nrows, int R, int nb, int sh, int width,
-                                                       const uint32_t *__restrict__ busy_in,
-                                                       uint32_t *__restrict__ busy_out, uint32_t *__restrict__ pre,
-                                                       uint32_t *__restrict__ need, uint32_t *__restrict__ ghist,
-                                                       uint32_t *__restrict__ gflag) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= nrows) return;
-    const int64_t u = i / R;
-    const int r = (int)(i % R);
-    if (busy_in && busy_in[u] == 0u) return;        // settled unit: its pass did not run, the bins are clear
-    uint32_t *h = ghist + u * nb * (int64_t)R + r;
-    const uint32_t nd = need[i];
-    uint32_t above = 0u, digit = 0u, rest = nd, in_bin = 0u;
-    bool found = false;
-    for (int b0 = (1 << width) - 1; b0 >= 0; b0 -= 8) {          // bins come in fours: 4, 32 or 64
-        uint32_t c[8];
+    uint32_t need = 0u;
+    float xa = INFINITY, xb = INFINITY, thr = INFINITY;    // nothing to gather
+    const int64_t kk = ts_rank(n, ratio_bp);
+    if (g.N >= W && kk == n) {
+        thr = -INFINITY;                                   // every key the row sees
+    } else if (g.N >= W) {
+        uint32_t *h = ws.hist + u * TS_BINS * (int64_t)R + r;
+        const float scale = ws.xa[i], off = ws.xb[i];
+        int64_t above = ws.above[i], rest = 0;
+        int bin = -1;
+        uint32_t in_bin = 0u;
+        const bool inside = above < kk;
+        const int64_t above_in = above;
+        for (int b0 = TS_BINS - 1; b0 >= 0; b0 -= 32) {
+            uint32_t c[32];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) c[j] = b0 - j >= 0 ? h[(int64_t)(b0 - j) * R] : 0u;
+            for (int j = 0; j < 32; ++j) c[j] = h[(int64_t)(b0 - j) * R];
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (b0 - j >= 0) h[(int64_t)(b0 - j) * R] = 0u;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (!found && b0 - j >= 0 && above + c[j] >= nd) {
-                found = true;
-                digit = (uint32_t)(b0 - j);
-                rest = nd - above;
-                in_bin = c[j];
+            for (int j = 0; j < 32; ++j) {
+                if (inside && bin < 0 && above + c[j] >= kk) {
+                    bin = b0 - j;
+                    rest = kk - above;
+                    in_bin = c[j];
+                }
+                above += c[j];
             }
-            above += c[j];
+        }
+        if (bin >= 0) {
+            xa = key_value(ts_bound(TS_LOW + 1 + bin, scale, off));
+            xb = key_value(ts_bound(TS_LOW + 2 + bin, scale, off) - 1u);
+        }
+        if (bin >= 0 && in_bin <= (uint32_t)TS_CMAX) {
+            need = (uint32_t)rest | in_bin << 16;
+        } else {
+            // another interval: the bin, or (the sample misjudged the row) the
+            // stretch above or below the last one
+            const float a = (1.f - off) / scale, w = 1.f / scale;
+            // keys above: few of them may lie far out
+            const float up = above_in <= 4 * TS_CMAX ? 16.f * w : w;
+            const float na = bin >= 0 ? xa : inside ? a - w : a + w;
+            const float nb = bin >= 0 ? xb + (xb - xa) * 1e-3f : inside ? a : a + w + up;
+            const float ns = 1.f / (nb - na), no = 1.f - na * ns;
+            if (!AGAIN && nb > na && ns > 0.f && ns < INFINITY && fabsf(no) < INFINITY) {
+                need = TS_AGAIN;
+                xa = ns;
+                xb = no;
+                ws.above[i] = 0u;
+                for (int d = 0; d < TS_BINS; ++d) h[(int64_t)d * R] = 0u;
+                ws.again[u] = 1u;                          // every writer stores the same value
+            } else {
+                need = TS_RADIX;
+                if (bin < 0) xa = xb = __builtin_nanf("");
+                atomicOr(ws.fail + u, 1u << (r / 32));
+            }
         }
     }
-    if (nd == 0u) return;
-    const uint32_t p = pre[i] | (digit << sh);
-    pre[i] = p;
-    const bool settled = rest == in_bin && p != 0x80000000u;      // +0 edge: -0 would tie it
-    const bool gather = !settled && gflag && in_bin <= (uint32_t)TS_CMAX;
-    need[i] = settled ? 0u : gather ? (rest | TS_GATHER) : rest;
-    // every writer of a flag stores the same value
-    if (gather) gflag[u] = 1u;
-    else if (!settled && busy_out) busy_out[u] = 1u;
+    ws.need[i] = need;
+    ws.xa[i] = xa;
+    ws.xb[i] = xb;
+    ws.thr[i] = thr;
 }
 
-// One block of the gather pass: the values of gathering rows whose key
-// matches the row's prefix (all bits above sh) are appended to the row's list
-// in LDS.  A value matches when (bits ^ c) < lim, where lim is 2^sh for a
-// gathering row and 0 otherwise: one compare per value, whose wavefront mask
-// (one bit per lane) is kept.  Matches are rare (a few per row over the whole
-// prompt), so they are handled behind one wavefront-uniform test per block.
-// The lanes holding one row (lane % BM) keep the row's count in step: a
-// value's mask gives every lane its slot (the count plus the set bits of its
-// row's lanes below it) and the count's increase, so no atomics are needed.
+// ---------------------------------------------------------------- gather
+
+// One block of the gather pass: the values of a row that lie in [xa, xb] are
+// appended to the lane's list in LDS (a row's values sit in the lanes of equal
+// lane % BM; each keeps its own).  Vector instructions only: the median of
+// (value, xa, xb) equals the value inside the interval; the lane keeps its
+// last match and a bit per value, and appends the match after the block.  A
+// lane with several matches in one block (one block in twenty has one) takes
+// them one by one.  (Masks per value, joined and tested in scalar registers,
+// took 254 us for the pass at 8K keys; a list entry turns up in nearly every
+// block.)
 template <typename T, int D, int NW, bool MASK>
 struct GatherStep {
-    static constexpr int NRB = QFrags<T, D>::NRB;
-    uint32_t *lcand;                // LDS [64 * NW][TS_CMAX]
-    uint32_t (&cnt)[NRB];           // values gathered so far for the lane's row
-    const uint32_t (&c)[NRB];       // as in HistStep
-    const uint32_t (&lim)[NRB];
+    using M = MT<T, D>;
+    static constexpr int NRB = QFrags<T, D>::NRB, CAP = TS_LIST * M::BM / 64;   // entries per lane and row block
+    uint32_t *mylist;               // LDS, this lane's: [NRB][CAP], words 64 apart
+    uint32_t (&cnt)[NRB];           // values gathered so far
+    const float (&xa)[NRB], (&xb)[NRB];
     const int (&pos)[NRB];
-    uint64_t rowmask, below;        // the lanes of the lane's row; those of them below the lane
-    int lane, wave, key0;
+    int lane, key0;
     __device__ __forceinline__ void operator()(TC<T, D> &acc, int kb, int rb) const {
-        using M = MT<T, D>;
-        uint64_t m[M::NV], any = 0u;
+        uint32_t hits = 0u;
+        float last = 0.f;
 #pragma unroll
         for (int v = 0; v < M::NV; ++v) {
-            bool h = (__float_as_uint(acc[v]) ^ c[rb]) < lim[rb];
+            bool h = __builtin_amdgcn_fmed3f(acc[v], xa[rb], xb[rb]) == acc[v];
             if (MASK) h = h && key0 + kb * M::BM + M::crow(v, lane) <= pos[rb];
-            m[v] = __ballot(h);
-            any |= m[v];
+            last = h ? acc[v] : last;
+            hits = hits + hits + (h ? 1u : 0u);
         }
-        if (__builtin_expect(any != 0u, 0)) {
-            const int row = wave * 64 + rb * M::BM + lane % M::BM;
+        auto add = [&](float x) {
+            if (cnt[rb] < (uint32_t)CAP) mylist[(rb * CAP + cnt[rb]) * 64] = __float_as_uint(x);
+            ++cnt[rb];
+        };
+        if (__any((hits & (hits - 1u)) != 0u)) {
 #pragma unroll
-            for (int v = 0; v < M::NV; ++v) {
-                if (m[v] == 0u) continue;           // wavefront-uniform
-                const uint32_t slot = cnt[rb] + (uint32_t)__popcll(m[v] & below);
-                if (((m[v] >> lane) & 1u) && slot < (uint32_t)TS_CMAX)
-                    lcand[row * TS_CMAX + slot] = __float_as_uint(acc[v]);
-                cnt[rb] += (uint32_t)__popcll(m[v] & rowmask);
-            }
+            for (int v = 0; v < M::NV; ++v)
+                if ((hits >> (M::NV - 1 - v)) & 1u) add(acc[v]);
+        } else if (hits != 0u) {
+            add(last);
         }
     }
 };
@@ -312,18 +566,18 @@ template <typename T, int D, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void ts_gather_kernel(
     int B, int L, int Hq, int Hkv, int W, const int32_t *__restrict__ cu_seqlens, int64_t T_,
     const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int nchunk, int chunk_keys,
-    int sh, const uint32_t *__restrict__ gflag, const uint32_t *__restrict__ pre, const uint32_t *__restrict__ need,
-    uint32_t *__restrict__ gcount, uint32_t *__restrict__ gcand) {
+    TsWork ws) {
     using M = MT<T, D>;
-    using KT = KTile<T, D>;
-    constexpr int NRB = QFrags<T, D>::NRB, ROWS = 64 * NW;
+    constexpr int TKEYS = ts_tile_keys<T>();
+    using KT = KTile<T, D, TKEYS>;
+    constexpr int NRB = QFrags<T, D>::NRB;
     __shared__ __attribute__((aligned(16))) char kbA[KT::BYTES];
     __shared__ __attribute__((aligned(16))) char kbB[KT::BYTES];
-    __shared__ uint32_t lcand[ROWS * TS_CMAX];
+    constexpr int CAP = GatherStep<T, D, NW, false>::CAP;
+    __shared__ uint32_t lists[NW * NRB * CAP * 64];
     int64_t u;
     int chunk;
     unit_chunk((int64_t)L * Hkv * B, nchunk, u, chunk);
-    if (gflag[u] == 0u) return;                 // no row of the unit gathers
     const UnitGeom g = unit_geom(u, B, Hkv, cu_seqlens, T_);
     const int G = Hq / Hkv, R = G * W;
     const int N = (int)g.N;
@@ -338,23 +592,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     KT::template load<NW>(kbA, kunit, key_begin, N, wave, lane);
     QFrags<T, D> q;
     q.load(qunit, R, wave, lane);
-    uint32_t c[NRB], cnt[NRB], lim[NRB];
+    uint32_t cnt[NRB];
+    float xa[NRB], xb[NRB];
     int pos[NRB];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
         const int row = wave * 64 + rb * M::BM + lane % M::BM;
         pos[rb] = row < R ? N - W + row % W : -1;
-        const uint32_t p = row < R ? pre[u * R + row] : 0u;
-        const bool on = row < R && (need[u * R + row] & TS_GATHER) != 0u;
-        lim[rb] = on ? 1u << sh : 0u;
-        c[rb] = p ^ ((p & 0x80000000u) ? 0x80000000u : 0xffffffffu);
+        const bool on = row < R && ws.need[u * R + row] != TS_RADIX;
+        xa[rb] = on ? ws.xa[u * R + row] : INFINITY;
+        xb[rb] = on ? ws.xb[u * R + row] : INFINITY;
         cnt[rb] = 0u;
     }
-    // lanes holding the same row: lane % BM, one per lane group
-    uint64_t rowmask = 0u;
-#pragma unroll
-    for (int gi = 0; gi < 64 / M::BM; ++gi) rowmask |= 1ull << (gi * M::BM + lane % M::BM);
-    const uint64_t below = rowmask & ((1ull << lane) - 1u);
+    uint32_t *mylist = lists + wave * (NRB * CAP * 64) + lane;
     TC<T, D> zero[NRB];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) zero[rb] = M::zero();
@@ -363,9 +613,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         barrier_after_loads();      // tile t landed; tile t - 1 done everywhere
         const int key0 = key_begin + t * KT::TK;
         if (t + 1 < ntile) KT::template load<NW>(nxt, kunit, key0 + KT::TK, N, wave, lane);
-        const GatherStep<T, D, NW, MASK> f{lcand, cnt, c, lim, pos, rowmask, below, lane, wave, key0};
-        if (MASK) tile_sweep_plain<T, D, true>(cur, q, zero, lane, f);
-        else tile_sweep<T, D, true>(cur, q, zero, lane, f);
+        const GatherStep<T, D, NW, MASK> f{mylist, cnt, xa, xb, pos, lane, key0};
+        if (MASK) tile_sweep_plain<T, D, true, TKEYS>(cur, q, zero, lane, f);
+        else tile_sweep<T, D, true, TKEYS>(cur, q, zero, lane, f);
     };
     const int nfull = full_tiles(key_begin, ntile, KT::TK, N, W);
     int t = 0;
@@ -378,90 +628,248 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         else step(t, kbA, kbB, std::true_type{});
     }
     barrier_after_loads();      // every list final, no load in flight
-    // the chunk's values go after those of the unit's other chunks (their order
-    // does not matter: the pick below ranks them); the first lane group of each
-    // row block writes its rows' lists
-    if (lane < M::BM) {
+    // a lane's values go after those the row already has (their order does not
+    // matter: the pick below ranks them)
 #pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) {
-            const int row = wave * 64 + rb * M::BM + lane;
-            const uint32_t n = min(cnt[rb], (uint32_t)TS_CMAX);
-            if (row >= R || n == 0u) continue;
-            const int64_t i = u * R + row;
-            const uint32_t base = __hip_atomic_fetch_add(gcount + i, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            for (uint32_t j = 0; j < n && base + j < (uint32_t)TS_CMAX; ++j)
-                gcand[i * TS_CMAX + base + j] = lcand[row * TS_CMAX + j];
-        }
+    for (int rb = 0; rb < NRB; ++rb) {
+        const int row = wave * 64 + rb * M::BM + lane % M::BM;
+        const uint32_t n = min(cnt[rb], (uint32_t)CAP);
+        if (row >= R || n == 0u) continue;
+        const int64_t i = u * R + row;
+        const uint32_t base = __hip_atomic_fetch_add(ws.gcount + i, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (uint32_t j = 0; j < n && base + j < (uint32_t)TS_CMAX; ++j)
+            ws.list[i * TS_CMAX + base + j] = mylist[(rb * CAP + j) * 64];
     }
 }
 
-// One thread per gathering row: the exact key of rank `need` (from the top)
-// among the gathered values; the row then settles on it.  The values wait in
-// LDS, so the loops run over the row's own count.
-__global__ __launch_bounds__(256) void ts_pick_kernel(int64_t nrows, const uint32_t *__restrict__ gcount,
-                                                      const uint32_t *__restrict__ gcand, uint32_t *__restrict__ pre,
-                                                      uint32_t *__restrict__ need) {
-    __shared__ uint32_t keys[TS_CMAX][256];
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= nrows) return;
-    const uint32_t nd = need[i];
-    if ((nd & TS_GATHER) == 0u) return;
-    const uint32_t rank = nd & ~TS_GATHER;
-    const int n = (int)min(gcount[i], (uint32_t)TS_CMAX);
-    uint32_t *kk = &keys[0][threadIdx.x];             // this thread's column: entries 256 words apart
-    for (int a = 0; a < n; ++a) {
-        const uint32_t x = gcand[i * TS_CMAX + a];
-        kk[a * 256] = x ^ ((uint32_t)((int32_t)x >> 31) | 0x80000000u);
+// The exact value of rank `need` (from the top) among a row's gathered ones: a
+// wavefront takes PICK_ROWS rows, all their loads issued first, a value (or
+// two) per lane, and finds every row's key bit by bit below the bits that the
+// bin's two ends share: the largest key that at least `rank` values reach.  A
+// list cut short (more matches in one chunk than a lane's list holds) sends
+// the row to the radix select.
+constexpr int PICK_ROWS = 8;
+__global__ __launch_bounds__(256) void ts_pick_kernel(int64_t nrows, int R, TsWork ws) {
+    const int lane = threadIdx.x % 64;
+    const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int64_t i0 = wave * PICK_ROWS;
+    if (i0 >= nrows) return;
+    const int64_t mine = min(i0 + lane % PICK_ROWS, nrows - 1);
+    uint32_t need = i0 + lane % PICK_ROWS < nrows ? ws.need[mine] : 0u;
+    const uint32_t got = ws.gcount[mine];
+    const uint32_t ka = order_key(ws.xa[mine]), kb = order_key(ws.xb[mine]);
+    uint32_t v0[PICK_ROWS], v1[PICK_ROWS];
+#pragma unroll
+    for (int j = 0; j < PICK_ROWS; ++j) {
+        const uint32_t *l = ws.list + min(i0 + j, nrows - 1) * TS_CMAX;
+        v0[j] = l[lane];
+        v1[j] = l[min(64 + lane, TS_CMAX - 1)];
     }
-    uint32_t best = pre[i];          // kept only if the values disagreed with the counts
-    for (int a = 0; a < n; ++a) {
-        const uint32_t ka = kk[a * 256];
-        uint32_t above = 0u, atleast = 0u;
-        for (int b = 0; b < n; ++b) {
-            const uint32_t kb = kk[b * 256];
-            above += kb > ka ? 1u : 0u;
-            atleast += kb >= ka ? 1u : 0u;
+    // lane j: row i0 + j
+    if (need == TS_RADIX) need = 0u;
+    if (need != 0u && got != need >> 16) {
+        const int64_t u = mine / R;
+        if (lane < PICK_ROWS) {
+            ws.need[mine] = TS_RADIX;
+            atomicOr(ws.fail + u, 1u << ((int)(mine % R) / 32));
         }
-        if (above < rank && rank <= atleast) best = ka;
+        need = 0u;
     }
-    pre[i] = best;
-    need[i] = 0u;
+    if (!__any(need != 0u)) return;
+    int rank[PICK_ROWS];
+    uint32_t cur[PICK_ROWS];
+    const int top = wave_max_bits(need != 0u ? ka ^ kb : 0u);      // bits to decide, of every row
+    bool two = false;                                   // some row has more than 64 values
+#pragma unroll
+    for (int j = 0; j < PICK_ROWS; ++j) {
+        const uint32_t nd = (uint32_t)__builtin_amdgcn_readlane((int)need, j);
+        const int n = (int)(nd >> 16);
+        rank[j] = (int)(nd & 0xffffu);
+        cur[j] = (uint32_t)__builtin_amdgcn_readlane((int)kb, j) & (top >= 32 ? 0u : ~0u << top);
+        v0[j] = lane < n ? order_key(__uint_as_float(v0[j])) : 0u;
+        v1[j] = 64 + lane < n ? order_key(__uint_as_float(v1[j])) : 0u;
+        two |= n > 64;
+    }
+    for (int bit = top - 1; bit >= 0; --bit) {
+#pragma unroll
+        for (int j = 0; j < PICK_ROWS; ++j) {
+            const uint32_t t = cur[j] | 1u << bit;
+            int c = (int)__popcll(__ballot(v0[j] >= t));
+            if (two) c += (int)__popcll(__ballot(v1[j] >= t));
+            cur[j] = c >= rank[j] ? t : cur[j];
+        }
+    }
+    float thr = 0.f;
+#pragma unroll
+    for (int j = 0; j < PICK_ROWS; ++j) thr = lane == j ? threshold_value(cur[j]) : thr;
+    if (lane < PICK_ROWS && need != 0u) ws.thr[mine] = thr;
 }
 
-// One block of the count pass: a ballot per value (bit = lane = row), whose
-// lane groups hold different keys; a key's picks in the block are the
-// population count of its lane group.  Four consecutive keys' counts go to
-// LDS in one write (lane 0), one slot per row block.
+// ---------------------------------------------------------------- radix
+
+// The exact thresholds of the rows that the passes above did not resolve, 32
+// rows of a unit per workgroup: 6-bit digits of the logits' order keys, most
+// significant first, below the bits that the ends of every such row's bin
+// share (a bin of ties is narrow by now: two or three digits), over all the
+// keys.
+constexpr int TS_RADIX_WAVES = 8, TS_RADIX_COPIES = 2;
+template <typename T, int D>
+__global__ __launch_bounds__(64 * TS_RADIX_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void ts_radix_kernel(
+    int B, int L, int Hq, int Hkv, int W, const int32_t *__restrict__ cu_seqlens, int64_t T_,
+    const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int ratio_bp, TsWork ws) {
+    using M = MT<T, D>;
+    constexpr int NB32 = 32 / M::BM;                   // row blocks
+    using KT = KTile<T, D, M::BM>;                     // one key block
+    __shared__ __attribute__((aligned(16))) char bufs[TS_RADIX_WAVES * 2 * KT::BYTES];
+    // two copies (with ties, wavefronts queue for one word); the last bin takes
+    // the keys that do not match the prefix
+    __shared__ uint32_t hist[TS_RADIX_COPIES][TS_BINS + 1][32];
+    __shared__ int over[32];                           // keys above the row's bin
+    __shared__ uint32_t prefix[32];
+    __shared__ int64_t rank[32];
+    __shared__ int bits;
+    const int R = (Hq / Hkv) * W, ngrp = (int)ceil_div(R, 32);
+    const int64_t u = blockIdx.x / ngrp;
+    const int grp = blockIdx.x % ngrp;
+    if (((ws.fail[u] >> grp) & 1u) == 0u) return;
+    const UnitGeom g = unit_geom(u, B, Hkv, cu_seqlens, T_);
+    const int N = (int)g.N, tid = threadIdx.x, lane = tid % 64;
+    if (N < W) return;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const T *qunit = q_win + (((int64_t)g.b * L + g.l) * Hq + (int64_t)g.h * (Hq / Hkv)) * W * D;
+    const T *kunit = k + ((int64_t)g.l * k_layer_rows + (int64_t)g.h * T_ + g.s0) * D;
+    TA<T, D> qf[NB32][M::KS];
+    int pos[NB32];
+#pragma unroll
+    for (int rb = 0; rb < NB32; ++rb) {
+        const int row = grp * 32 + rb * M::BM + lane % M::BM;
+        pos[rb] = row < R ? N - W + row % W : -1;
+        const T *p = qunit + (int64_t)min(row, R - 1) * D;
+#pragma unroll
+        for (int ks = 0; ks < M::KS; ++ks) qf[rb][ks] = M::load_global(p, ks, lane);
+    }
+    const int64_t myrow = u * R + grp * 32 + tid;
+    const bool mine = tid < 32 && grp * 32 + tid < R && ws.need[myrow] == TS_RADIX;
+    if (tid < 64) {
+        uint32_t ka = 0u, diff = 0u;
+        if (mine) {
+            const float xa = ws.xa[myrow], xb = ws.xb[myrow];
+            ka = order_key(xa);
+            diff = xa <= xb ? ka ^ order_key(xb) : ~0u;        // NaN: nothing known
+        }
+        const int nbits = wave_max_bits(diff);
+        if (tid < 32) {
+            prefix[tid] = nbits < 32 ? ka >> nbits << nbits : 0u;
+            over[tid] = 0;
+            rank[tid] = ts_rank(N - W + (grp * 32 + tid) % W + 1, ratio_bp);
+        }
+        if (tid == 0) bits = nbits;
+    }
+    __syncthreads();
+    const int hi0 = __builtin_amdgcn_readfirstlane(bits);
+    char *mybuf = bufs + wave * (2 * KT::BYTES);
+    for (int hi = hi0; hi > 0;) {
+        const int sh = max(0, hi - 6);
+        for (int i = tid; i < TS_RADIX_COPIES * (TS_BINS + 1) * 32; i += 64 * TS_RADIX_WAVES) (&hist[0][0][0])[i] = 0u;
+        __syncthreads();
+        // no branch per value: one whose key does not match the row's prefix
+        // adds to the last bin.  For a prefix that holds the sign bit, the
+        // value's bits ^ flip = its key ^ prefix.
+        const uint32_t lim = 1u << (hi - sh);
+        uint32_t flip[NB32], end[NB32];
+        int above[NB32];
+#pragma unroll
+        for (int rb = 0; rb < NB32; ++rb) {
+            const uint32_t p = prefix[rb * M::BM + lane % M::BM];
+            flip[rb] = p ^ ((p & 0x80000000u) ? 0x80000000u : 0xffffffffu);
+            end[rb] = hi < 32 ? p | ((1u << hi) - 1u) : ~0u;
+            above[rb] = 0;
+        }
+        // every wavefront streams its own key blocks through two LDS buffers,
+        // the next one's loads in flight (straight from memory each lane would
+        // read pieces of its own key's row, and the rows of several wavefronts
+        // do not fit the L1)
+        if (wave * M::BM < N) KT::template load<1>(mybuf, kunit, wave * M::BM, N, 0, lane);
+        for (int key0 = wave * M::BM, t = 0; key0 < N; key0 += TS_RADIX_WAVES * M::BM, ++t) {      // uniform per wavefront
+            const char *cur = mybuf + (t & 1) * KT::BYTES;
+            KT::template load<1>(mybuf + (~t & 1) * KT::BYTES, kunit, min(key0 + TS_RADIX_WAVES * M::BM, N - 1), N, 0, lane);
+            wait_vmem<KT::BYTES / 1024>();
+            {
+                TA<T, D> kf[M::KS];
+#pragma unroll
+                for (int ks = 0; ks < M::KS; ++ks) kf[ks] = KT::frag(cur, 0, ks, lane);
+#pragma unroll
+                for (int rb = 0; rb < NB32; ++rb) {
+                    const TC<T, D> acc = block_mma<T, D, true>(kf, qf[rb]);
+#pragma unroll
+                    for (int v = 0; v < M::NV; ++v) {
+                        const bool sees = key0 + M::crow(v, lane) <= pos[rb];
+                        const uint32_t y = hi == 32 ? order_key(acc[v]) : __float_as_uint(acc[v]) ^ flip[rb];
+                        const uint32_t d = sees ? min(y >> sh, lim) : lim;
+                        if (hi == hi0) above[rb] += sees && order_key(acc[v]) > end[rb] ? 1 : 0;
+                        __hip_atomic_fetch_add(&hist[wave % TS_RADIX_COPIES][d][rb * M::BM + lane % M::BM], 1u, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                }
+            }
+        }
+        wait_vmem<0>();
+        if (hi == hi0)
+#pragma unroll
+            for (int rb = 0; rb < NB32; ++rb) atomicAdd(&over[rb * M::BM + lane % M::BM], above[rb]);
+        __syncthreads();
+        if (tid < 32) {
+            int64_t above = hi == hi0 ? over[tid] : 0;
+            const int64_t want = rank[tid];
+            for (int d = (1 << (hi - sh)) - 1; d >= 0; --d) {
+                int64_t c = 0;
+#pragma unroll
+                for (int w = 0; w < TS_RADIX_COPIES; ++w) c += hist[w][d][tid];
+                if (above < want && want <= above + c) {
+                    prefix[tid] |= (uint32_t)d << sh;
+                    rank[tid] = want - above;
+                }
+                above += c;
+            }
+        }
+        __syncthreads();
+        hi = sh;
+    }
+    if (mine) ws.thr[myrow] = threshold_value(prefix[tid]);
+}
+
+// ---------------------------------------------------------------- count
+
+// Keys per LDS tile of the count pass.
+template <typename T>
+constexpr int ts_count_tile_keys() { return sizeof(T) == 2 ? 128 : 64; }
+
+// One block of the count pass, C = Q K^T: a lane's values belong to one key,
+// and a key's picks are added up in the lane.
 template <typename T, int D, bool MASK>
 struct TsCountStep {
-    static constexpr int NRB = QFrags<T, D>::NRB, GR = 64 / MT<T, D>::BM;
-    uint32_t *cs;                          // LDS [NRB][tile keys]: this wavefront's picks
-    const float (&thr)[NRB];               // the lane's row's threshold (+inf: padded row)
-    const int (&pos)[NRB];
-    int lane, key0;
+    static constexpr int NRB = QFrags<T, D>::NRB;
+    int (&cs)[KTile<T, D, ts_count_tile_keys<T>()>::NKB];
+    const TC<T, D> (&thr)[NRB];            // the thresholds of the lane's rows (+inf: padded row)
+    const int *poss;                       // window position of every row of the unit (-1: padded), LDS
+    int lane, wave, key0;
     __device__ __forceinline__ void operator()(TC<T, D> &acc, int kb, int rb) const {
         using M = MT<T, D>;
-        constexpr uint32_t GMASK = (uint32_t)((1ull << M::BM) - 1);
+        const int key = key0 + kb * M::BM + lane % M::BM;
+        int n[2] = {0, 0};
 #pragma unroll
-        for (int v4 = 0; v4 < M::NV / 4; ++v4) {
-            uint32_t n[GR][4];
+        for (int g4 = 0; g4 < M::NV / 4; ++g4) {
+            int4 pos = make_int4(0, 0, 0, 0);
+            if (MASK) pos = *reinterpret_cast<const int4 *>(poss + wave * 64 + rb * M::BM + M::crow(4 * g4, lane));
+            const int ps[4] = {pos.x, pos.y, pos.z, pos.w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int v = 4 * v4 + i;
-                bool pick = acc[v] >= thr[rb];
-                if (MASK) pick = pick && key0 + kb * M::BM + M::crow(v, lane) <= pos[rb];
-                const uint64_t m = __ballot(pick);
-#pragma unroll
-                for (int gi = 0; gi < GR; ++gi) n[gi][i] = (uint32_t)__popc((uint32_t)(m >> (gi * M::BM)) & GMASK);
-            }
-            // keys crow(4 v4 + i, gi * BM), i = 0..3, are consecutive
-            if (lane == 0) {
-#pragma unroll
-                for (int gi = 0; gi < GR; ++gi)
-                    *reinterpret_cast<uint4 *>(cs + rb * KTile<T, D>::TK + kb * M::BM + M::crow(4 * v4, gi * M::BM)) =
-                        make_uint4(n[gi][0], n[gi][1], n[gi][2], n[gi][3]);
+                bool pick = acc[4 * g4 + i] >= thr[rb][4 * g4 + i];
+                if (MASK) pick = pick && key <= ps[i];
+                n[i % 2] += pick ? 1 : 0;
             }
         }
+        cs[kb] += n[0] + n[1];
     }
 };
 
@@ -469,13 +877,16 @@ template <typename T, int D, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void ts_count_kernel(
     int B, int L, int Hq, int Hkv, int W, const int32_t *__restrict__ cu_seqlens, int64_t T_,
     const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int nchunk, int chunk_keys,
-    const uint32_t *__restrict__ pre, float *__restrict__ counts) {
+    const float *__restrict__ thr_rows, float *__restrict__ counts) {
     using M = MT<T, D>;
-    using KT = KTile<T, D>;
-    constexpr int NRB = QFrags<T, D>::NRB;
+    constexpr int TKEYS = ts_count_tile_keys<T>();
+    using KT = KTile<T, D, TKEYS>;
+    constexpr int NRB = QFrags<T, D>::NRB, NKB = KT::NKB;
     __shared__ __attribute__((aligned(16))) char kbA[KT::BYTES];
     __shared__ __attribute__((aligned(16))) char kbB[KT::BYTES];
-    __shared__ __attribute__((aligned(16))) uint32_t csum[2][NW][NRB][KT::TK];
+    __shared__ int csum[2][NW][KT::TK];
+    __shared__ __attribute__((aligned(16))) float thr_s[NW * 64];
+    __shared__ __attribute__((aligned(16))) int poss[NW * 64];
     int64_t u;
     int chunk;
     unit_chunk((int64_t)L * Hkv * B, nchunk, u, chunk);
@@ -498,25 +909,25 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     KT::template load<NW>(kbA, kunit, key_begin, N, wave, lane);
     QFrags<T, D> q;
     q.load(qunit, R, wave, lane);
-    float thr[NRB];
-    int pos[NRB];
+    for (int r = threadIdx.x; r < NW * 64; r += 64 * NW) {
+        thr_s[r] = r < R ? thr_rows[u * R + r] : INFINITY;
+        poss[r] = r < R ? N - W + r % W : -1;
+    }
+    __syncthreads();
+    TC<T, D> zero[NRB], thr[NRB];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
-        const int row = wave * 64 + rb * M::BM + lane % M::BM;
-        pos[rb] = row < R ? N - W + row % W : -1;
-        thr[rb] = row < R ? threshold_value(pre[u * R + row]) : INFINITY;
-    }
-    TC<T, D> zero[NRB];
+        zero[rb] = M::zero();
 #pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) zero[rb] = M::zero();
+        for (int v = 0; v < M::NV; ++v) thr[rb][v] = thr_s[wave * 64 + rb * M::BM + M::crow(v, lane)];
+    }
     // the wavefronts' picks of tile t sit in csum[t & 1]; they are added and
     // stored after the next barrier
     auto flush = [&](int t) {
         const int key0 = key_begin + t * KT::TK;
         for (int j = threadIdx.x; j < KT::TK; j += 64 * NW) {
-            uint32_t v = 0u;
-            for (int w = 0; w < NW; ++w)
-                for (int rb = 0; rb < NRB; ++rb) v += csum[t & 1][w][rb][j];
+            int v = 0;
+            for (int w = 0; w < NW; ++w) v += csum[t & 1][w][j];
             if (key0 + j < N) orow[key0 + j] = (float)v;
         }
     };
@@ -526,9 +937,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (t > 0) flush(t - 1);
         const int key0 = key_begin + t * KT::TK;
         if (t + 1 < ntile) KT::template load<NW>(nxt, kunit, key0 + KT::TK, N, wave, lane);
-        const TsCountStep<T, D, MASK> f{&csum[t & 1][wave][0][0], thr, pos, lane, key0};
-        if (MASK) tile_sweep_plain<T, D, true>(cur, q, zero, lane, f);
-        else tile_sweep<T, D, true>(cur, q, zero, lane, f);
+        int cs[NKB];
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) cs[kb] = 0;
+        const TsCountStep<T, D, MASK> f{cs, thr, poss, lane, wave, key0};
+        if (MASK) tile_sweep_plain<T, D, false, TKEYS>(cur, q, zero, lane, f);
+        else tile_sweep<T, D, false, TKEYS>(cur, q, zero, lane, f);
+        // lanes holding the same key (different rows) add up; every such lane
+        // then holds the total and stores it
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+#pragma unroll
+            for (int off = M::BM; off < 64; off <<= 1) cs[kb] += __shfl_xor(cs[kb], off, 64);
+            csum[t & 1][wave][kb * M::BM + lane % M::BM] = cs[kb];
+        }
     };
     const int nfull = full_tiles(key_begin, ntile, KT::TK, N, W);
     int t = 0;
@@ -540,56 +962,53 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (t & 1) step(t, kbB, kbA, std::true_type{});
         else step(t, kbA, kbB, std::true_type{});
     }
-    barrier_after_loads();
+    __syncthreads();
     flush(ntile - 1);
 }
 
 template <typename T, int D, int NW>
 static void launch_topshare(hipStream_t s, const ScorePlan &p, int B, int L, int Hq, int Hkv, int W,
-                            const int32_t *cu_seqlens, int64_t ntok, const void *q_win, const void *k,
-                            int64_t k_layer_rows, int ratio_bp, float *counts, void *ws) {
-    constexpr int DB = TsDigits<NW>::DB, NB = TsDigits<NW>::NB;
+                            const int32_t *cu_seqlens, int64_t ntok, int max_seqlen, const void *q_win,
+                            const void *k, int64_t k_layer_rows, int ratio_bp, float *counts, void *wsp) {
     const int R = (Hq / Hkv) * W;
     const int64_t units = (int64_t)L * Hkv * B, nrows = units * R;
-    uint32_t *pre = reinterpret_cast<uint32_t *>(ws);
-    uint32_t *need = pre + nrows;
-    uint32_t *gh = need + nrows;
-    uint32_t *busy = gh + nrows * TS_MAXBINS;               // [TS_MAXPASS][units]
-    uint32_t *gflag = busy + TS_MAXPASS * units;            // [units]
-    uint32_t *gcount = gflag + units;                       // [rows]
-    uint32_t *gcand = gcount + nrows;                       // [rows][TS_CMAX]
+    TsWork ws;
+    ws.xa = reinterpret_cast<float *>(wsp);
+    ws.xb = ws.xa + nrows;
+    ws.need = reinterpret_cast<uint32_t *>(ws.xb + nrows);
+    ws.above = ws.need + nrows;
+    ws.gcount = ws.above + nrows;
+    ws.thr = reinterpret_cast<float *>(ws.gcount + nrows);
+    ws.hist = reinterpret_cast<uint32_t *>(ws.thr + nrows);
+    ws.list = ws.hist;
+    ws.fail = ws.hist + nrows * TS_CMAX;
+    ws.again = ws.fail + units;
     const T *q = reinterpret_cast<const T *>(q_win);
     const T *kk = reinterpret_cast<const T *>(k);
-    const dim3 rgrid((unsigned)ceil_div(nrows, 256));
     const dim3 grid((unsigned)(units * p.nchunk));
-    static_assert((32 + DB - 1) / DB <= TS_MAXPASS, "flag words");
-    ts_init_kernel<<<rgrid, 256, 0, s>>>(nrows, R, W, B, Hkv, cu_seqlens, ntok, ratio_bp, pre, need, gh, NB, busy,
-                                         units, gcount, gflag);
-    for (int pass = 0, hi = 32; hi > 0; ++pass) {
-        const int sh = std::max(0, hi - DB), width = hi - sh;
-        const uint32_t *busy_in = pass > 0 ? busy + (pass - 1) * units : nullptr;
-        uint32_t *busy_out = sh > 0 ? busy + pass * units : nullptr;
-        if (pass == 0)
-            ts_hist_kernel<T, D, NW, true><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk,
-                                                                  k_layer_rows, p.nchunk, p.chunk_keys, sh, width,
-                                                                  busy_in, pre, gh);
-        else
-            ts_hist_kernel<T, D, NW, false><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk,
-                                                                   k_layer_rows, p.nchunk, p.chunk_keys, sh, width,
-                                                                   busy_in, pre, gh);
-        const bool gather = 32 - sh >= TS_GATHER_BITS && 32 - hi < TS_GATHER_BITS;   // first digit past 18 bits
-        ts_digit_kernel<<<rgrid, 256, 0, s>>>(nrows, R, NB, sh, width, busy_in, busy_out, pre, need, gh,
-                                              gather ? gflag : nullptr);
-        if (gather) {
-            ts_gather_kernel<T, D, NW><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk,
-                                                               k_layer_rows, p.nchunk, p.chunk_keys, sh, gflag, pre,
-                                                               need, gcount, gcand);
-            ts_pick_kernel<<<rgrid, 256, 0, s>>>(nrows, gcount, gcand, pre, need);
-        }
-        hi = sh;
-    }
+    // a larger sample for longer prompts: the interval, and so a bin, then holds
+    // about as many keys (8K keys: about 22 of the 92 a row may gather; 32K: 45)
+#define SG_SAMPLE(NWV, ROWS)                                                                            \
+    ts_sample_kernel<T, D, NWV, ROWS><<<(unsigned)(units * ceil_div(R, ROWS)), 64 * NWV, 0, s>>>(        \
+        B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows, ratio_bp, ws)
+    if (max_seqlen <= 12288) SG_SAMPLE(4, 64);             // 512 keys
+    else if (max_seqlen <= 24576) SG_SAMPLE(8, 64);        // 1024
+    else SG_SAMPLE(8, 32);                                 // 2048
+#undef SG_SAMPLE
+    const dim3 dgrid((unsigned)units, (unsigned)ceil_div(R, TS_DIGIT_THREADS));
+    ts_hist_kernel<T, D, NW, false><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows,
+                                                             p.nchunk, p.chunk_keys, ws);
+    ts_digit_kernel<false><<<dgrid, TS_DIGIT_THREADS, 0, s>>>(R, W, B, Hkv, cu_seqlens, ntok, ratio_bp, ws);
+    ts_hist_kernel<T, D, NW, true><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows,
+                                                            p.nchunk, p.chunk_keys, ws);
+    ts_digit_kernel<true><<<dgrid, TS_DIGIT_THREADS, 0, s>>>(R, W, B, Hkv, cu_seqlens, ntok, ratio_bp, ws);
+    ts_gather_kernel<T, D, NW><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows,
+                                                        p.nchunk, p.chunk_keys, ws);
+    ts_pick_kernel<<<(unsigned)ceil_div(nrows, 4 * PICK_ROWS), 256, 0, s>>>(nrows, R, ws);
+    ts_radix_kernel<T, D><<<(unsigned)(units * ceil_div(R, 32)), 64 * TS_RADIX_WAVES, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q,
+                                                                             kk, k_layer_rows, ratio_bp, ws);
     ts_count_kernel<T, D, NW><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows,
-                                                      p.nchunk, p.chunk_keys, pre, counts);
+                                                      p.nchunk, p.chunk_keys, ws.thr, counts);
 }
 
 template <typename T, int D>
@@ -599,10 +1018,10 @@ static int topshare_dispatch(hipStream_t s, int B, int L, int Hq, int Hkv, int W
     const int R = (Hq / Hkv) * W;
     const int nw = (int)ceil_div(R, 64);
     const ScorePlan p = score_plan(B, L, Hkv, max_seqlen);
-    if (nw <= 1) launch_topshare<T, D, 1>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, q_win, k, k_layer_rows, ratio_bp, counts, ws);
-    else if (nw <= 2) launch_topshare<T, D, 2>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, q_win, k, k_layer_rows, ratio_bp, counts, ws);
-    else if (nw <= 4) launch_topshare<T, D, 4>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, q_win, k, k_layer_rows, ratio_bp, counts, ws);
-    else launch_topshare<T, D, 8>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, q_win, k, k_layer_rows, ratio_bp, counts, ws);
+    if (nw <= 1) launch_topshare<T, D, 1>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, max_seqlen, q_win, k, k_layer_rows, ratio_bp, counts, ws);
+    else if (nw <= 2) launch_topshare<T, D, 2>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, max_seqlen, q_win, k, k_layer_rows, ratio_bp, counts, ws);
+    else if (nw <= 4) launch_topshare<T, D, 4>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, max_seqlen, q_win, k, k_layer_rows, ratio_bp, counts, ws);
+    else launch_topshare<T, D, 8>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, max_seqlen, q_win, k, k_layer_rows, ratio_bp, counts, ws);
     return launch_status("sg_score_topshare");
 }
 
@@ -613,7 +1032,7 @@ using namespace sg;
 extern "C" size_t sg_score_topshare_workspace_size(int B, int L, int Hq, int Hkv, int d, int W, int max_seqlen) {
     if (B <= 0 || L <= 0 || Hkv <= 0 || Hq <= 0 || W <= 0 || max_seqlen <= 0 || d <= 0) return 0;
     const int64_t units = (int64_t)L * Hkv * B, rows = units * (Hq / Hkv) * W;
-    return (size_t)(rows * (3 + TS_MAXBINS + TS_CMAX) + units * (TS_MAXPASS + 1)) * sizeof(uint32_t);
+    return (size_t)(rows * TS_ROW_WORDS + units * TS_UNIT_WORDS) * sizeof(uint32_t);
 }
 
 extern "C" int sg_score_topshare(void *stream, sg_dtype dt, int B, int L, int Hq, int Hkv, int d, int W,

@@ -1,0 +1,43 @@
+"""GPU parity of sg_score_topshare where its passes hand a row on: each sample
+size, intervals misjudged or widened by far outliers, bins of ties that reach
+the radix select, ranks at both ends, short requests beside long ones.  Inputs
+are integers, so every logit is exact in fp32 and fp64 and the counts must
+equal the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests.gpu_util import say
+from tests.test_gpu_selectors import _ints, _topshare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,G,W,d,lens,bp,kind", [
+    ("bf16", 4, 64, 64, (12288,), 2000, "plain"),        # 512 sampled keys
+    ("bf16", 4, 64, 64, (12289, 700), 2000, "plain"),    # 1024
+    ("bf16", 1, 33, 128, (24577, 40, 3000), 4000, "plain"),   # 2048, requests far shorter, N just above W
+    ("f32", 2, 16, 64, (24577,), 1000, "plain"),
+    ("bf16", 4, 64, 64, (9000,), 2000, "outliers"),      # the sample's range is mostly empty
+    ("bf16", 4, 64, 64, (9000,), 1, "outliers"),         # the maxima
+    ("bf16", 4, 40, 64, (8191,), 9999, "plain"),         # nearly every key
+    ("bf16", 2, 64, 64, (5000, 513), 2000, "ties"),      # a few distinct logits
+    ("f32", 4, 16, 64, (3000,), 5000, "ties"),
+    ("bf16", 4, 64, 64, (4096,), 2000, "zeros"),         # one logit
+    ("bf16", 4, 64, 64, (9001,), 3000, "half"),          # half the keys tied at zero
+    ("bf16", 8, 64, 128, (4097,), 2000, "plain"),        # 512 rows
+])
+def test_topshare_paths_exact(gpu_lib, dtype, G, W, d, lens, bp, kind):
+    say("topshare paths", dtype, G, W, d, lens, bp, kind)
+    L, Hkv, T = 1, 2, sum(lens)
+    span = 1 if kind == "ties" else 0 if kind == "zeros" else 40
+    q = _ints((len(lens), L, Hkv * G, W, d), -max(span, 1), max(span, 1), T + W, dtype)
+    k = _ints((L, Hkv, T, d), -span, span, T + d, dtype)
+    if kind == "outliers":                               # still exact: below 2^24
+        k[:, :, ::1500] *= 32
+    if kind == "half":
+        k[:, :, ::2] = 0
+    got, cus = _topshare(gpu_lib, q, k, lens, Hkv, bp)
+    ref = oracle.score_topshare(q.float().numpy(), k.float().numpy(), cus, Hkv, bp)
+    np.testing.assert_array_equal(got, ref.astype(np.float32))
