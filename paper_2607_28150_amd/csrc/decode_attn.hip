@@ -633,30 +633,55 @@ __global__ __launch_bounds__((64 * DecodeShape<T, D, HG>::WAVES)) void decode_ke
     }
 }
 
+constexpr int DEC_MERGE_GROUP = 8;      // split states whose loads are in flight together
+
 // Combines the states of a unit's splits; splits that start at or past the
 // unit's (clamped) row count wrote none and are skipped.  split_rows == 0:
-// equal parts, all of which a unit with rows wrote.
+// equal parts, all of which a unit with rows wrote.  Latency alone: with the
+// states' loads in flight together a merge of seven splits takes 3.6 us, one
+// after another they took 6.3 (one request's layer call: 13.1 -> 12.0 us).
 template <int D, int G>
 __global__ __launch_bounds__(256) void decode_merge_kernel(int Hq, int Hkv, int nsplit, const int32_t *__restrict__ n_rows,
                                                           int64_t max_rows, int64_t split_rows,
                                                           const float *__restrict__ ws, float *__restrict__ out) {
     const int64_t unit = blockIdx.x;
     const int b = (int)(unit / Hkv), h = (int)(unit % Hkv);
-    const int64_t n = max<int64_t>(0, min<int64_t>(n_rows[unit], max_rows));
-    const int used = split_rows > 0 ? (int)min<int64_t>(nsplit, ceil_div(n, split_rows)) : (n > 0 ? nsplit : 0);
     float *w = const_cast<float *>(ws);
     for (int i = threadIdx.x; i < G * D; i += 256) {
         const int g = i / D, c = i % D;
+        // DEC_MERGE_GROUP states' loads at a time, all in flight together
+        // (the first group's beside the row count's: a state that no split
+        // wrote is loaded and left out); the sums keep the splits' order
+        auto load = [&](int s0, float (&m)[DEC_MERGE_GROUP], float (&l)[DEC_MERGE_GROUP], float (&o)[DEC_MERGE_GROUP]) {
+#pragma unroll
+            for (int j = 0; j < DEC_MERGE_GROUP; ++j) {
+                const float *pp = part_ptr(w, unit, nsplit, min(s0 + j, nsplit - 1), G, D) + (int64_t)g * (D + 2);
+                m[j] = pp[0];
+                l[j] = pp[1];
+                o[j] = pp[2 + c];
+            }
+        };
+        float m[DEC_MERGE_GROUP], l[DEC_MERGE_GROUP], o[DEC_MERGE_GROUP];
+        load(0, m, l, o);
+        __builtin_amdgcn_sched_barrier(0);
+        const int64_t n = max<int64_t>(0, min<int64_t>(n_rows[unit], max_rows));
+        const int used = split_rows > 0 ? (int)min<int64_t>(nsplit, ceil_div(n, split_rows)) : (n > 0 ? nsplit : 0);
         float M = -INFINITY;
-        for (int s = 0; s < used; ++s) M = fmaxf(M, part_ptr(w, unit, nsplit, s, G, D)[g * (D + 2)]);
+#pragma unroll
+        for (int j = 0; j < DEC_MERGE_GROUP; ++j) M = j < used ? fmaxf(M, m[j]) : M;
+        for (int s = DEC_MERGE_GROUP; s < used; ++s)
+            M = fmaxf(M, part_ptr(w, unit, nsplit, s, G, D)[(int64_t)g * (D + 2)]);
         float Lsum = 0.f, O = 0.f;
         if (M > -INFINITY) {
-            for (int s = 0; s < used; ++s) {
-                const float *pp = part_ptr(w, unit, nsplit, s, G, D) + (int64_t)g * (D + 2);
-                if (pp[0] > -INFINITY) {
-                    const float a = __builtin_amdgcn_exp2f(pp[0] - M);
-                    Lsum += a * pp[1];
-                    O += a * pp[2 + c];
+            for (int s0 = 0; s0 < used; s0 += DEC_MERGE_GROUP) {
+                if (s0 > 0) load(s0, m, l, o);
+#pragma unroll
+                for (int j = 0; j < DEC_MERGE_GROUP; ++j) {
+                    if (s0 + j < used && m[j] > -INFINITY) {
+                        const float a = __builtin_amdgcn_exp2f(m[j] - M);
+                        Lsum += a * l[j];
+                        O += a * o[j];
+                    }
                 }
             }
         }
