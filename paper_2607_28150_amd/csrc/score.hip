@@ -151,7 +151,7 @@ struct StatsMax {
     }
 };
 
-template <typename T, int D, int NW, bool MAXONLY>
+template <typename T, int D, int NW, bool MAXONLY, int NRBU>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(stats_waves<T>(MAXONLY)))) void score_stats_kernel(
     int B, int L, int Hq, int Hkv, int W, const int32_t *__restrict__ cu_seqlens, int64_t T_,
     const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, float c2, int nchunk, int chunk_keys,
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(stats_w
     const int ntile = (int)ceil_div(key_end - key_begin, KT::TK);
     KT::template load<NW>(kbA, kunit, key_begin, N, wave, lane);
     QFrags<T, D> q;
-    q.load(qunit, R, wave, lane);
+    q.template load<NRBU>(qunit, R, wave, lane);
 
     TC<T, D> zero[NRB];
 #pragma unroll
@@ -199,20 +199,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(stats_w
     };
     auto full = [&](const char *buf, int key0) {       // every row sees every key of the tile
         if constexpr (MAXONLY) {
-            tile_sweep<T, D, true, SC_STATS_TILE_KEYS>(buf, q, zero, lane, StatsMax<T, D, false>{m, lane, wave, key0, N, W, R});
+            tile_sweep<T, D, true, SC_STATS_TILE_KEYS, NRBU>(buf, q, zero, lane, StatsMax<T, D, false>{m, lane, wave, key0, N, W, R});
         } else {
             unsigned need = 0u;
-            tile_sweep<T, D, true, SC_STATS_TILE_KEYS>(buf, q, zero, lane, StatsFast<T, D>{m, s, need, c2});
+            tile_sweep<T, D, true, SC_STATS_TILE_KEYS, NRBU>(buf, q, zero, lane, StatsFast<T, D>{m, s, need, c2});
             if (__any(need != 0u))             // rare: those blocks again, exactly
-                tile_sweep<T, D, true, SC_STATS_TILE_KEYS>(buf, q, zero, lane,
+                tile_sweep<T, D, true, SC_STATS_TILE_KEYS, NRBU>(buf, q, zero, lane,
                                        StatsExact<T, D, false>{m, s, need, lane, wave, key0, N, W, R, c2});
         }
     };
     auto masked = [&](const char *buf, int key0) {     // causal limit and prompt end (or a leftover full tile)
         if constexpr (MAXONLY)
-            tile_sweep_plain<T, D, true, SC_STATS_TILE_KEYS>(buf, q, zero, lane, StatsMax<T, D, true>{m, lane, wave, key0, N, W, R});
+            tile_sweep_plain<T, D, true, SC_STATS_TILE_KEYS, NRBU>(buf, q, zero, lane, StatsMax<T, D, true>{m, lane, wave, key0, N, W, R});
         else
-            tile_sweep_plain<T, D, true, SC_STATS_TILE_KEYS>(buf, q, zero, lane,
+            tile_sweep_plain<T, D, true, SC_STATS_TILE_KEYS, NRBU>(buf, q, zero, lane,
                                          StatsExact<T, D, true>{m, s, ~0u, lane, wave, key0, N, W, R, c2});
     };
     const int nfull = full_tiles(key_begin, ntile, KT::TK, N, W);
@@ -245,7 +245,40 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(stats_w
 
 // ---------------------------------------------------------------- colsum pass
 
-// Column sums of one block: cs[kb] += sum over the lane's rows of exp(z - LSE).
+// A row's chunk statistics pr[c * R], c < nc: SC_MERGE chunks' loads are in
+// flight together (one after another they cost a memory round trip each: with
+// 16 chunks, half of a small call's colsum pass).  The sums keep the chunks'
+// order.
+constexpr int SC_MERGE = 16;
+__device__ __forceinline__ void merge_load(const float2 *pr, int c0, int nc, int R, float2 (&p)[SC_MERGE]) {
+#pragma unroll
+    for (int j = 0; j < SC_MERGE; ++j) p[j] = pr[(int64_t)min(c0 + j, nc - 1) * R];
+}
+__device__ __forceinline__ float merge_max(const float2 *pr, int nc, int R) {
+    float Mx = -INFINITY;
+    for (int c0 = 0; c0 < nc; c0 += SC_MERGE) {
+        float2 p[SC_MERGE];
+        merge_load(pr, c0, nc, R, p);
+#pragma unroll
+        for (int j = 0; j < SC_MERGE; ++j) Mx = fmaxf(Mx, p[j].x);      // (the last chunk's repeats change nothing)
+    }
+    return Mx;
+}
+// log2 of the row's sum of exponentials; +inf for a row without any
+__device__ __forceinline__ float merge_lse(const float2 *pr, int nc, int R) {
+    const float Mx = merge_max(pr, nc, R);
+    const float ref = Mx == -INFINITY ? 0.f : Mx;
+    float S = 0.f;
+    for (int c0 = 0; c0 < nc; c0 += SC_MERGE) {
+        float2 p[SC_MERGE];
+        merge_load(pr, c0, nc, R, p);
+#pragma unroll
+        for (int j = 0; j < SC_MERGE; ++j)
+            if (c0 + j < nc) S += p[j].y * __builtin_amdgcn_exp2f(p[j].x - ref);
+    }
+    return S > 0.f ? ref + __log2f(S) : INFINITY;
+}
+
 // Column sums of one block: cs[kb] += sum over the lane's rows of
 // exp2(c2 * acc), where the products were accumulated onto minus each row's
 // normaliser (divided by c2), so acc * c2 = z * c2 - LSE_row in log2 units.
@@ -262,7 +295,9 @@ struct ColsumStep {
         const int key = key0 + kb * M::BM + lane % M::BM;
         // four independent partial sums (one long chain of dependent adds
         // would stall the wavefront), combined in a fixed order
+        // (count mode: integer picks, one compare and one add with carry each)
         float t[4] = {0.f, 0.f, 0.f, 0.f};
+        int n[2] = {0, 0};
 #pragma unroll
         for (int g4 = 0; g4 < M::NV / 4; ++g4) {
             int4 pos = make_int4(0, 0, 0, 0);
@@ -270,16 +305,21 @@ struct ColsumStep {
             const int ps[4] = {pos.x, pos.y, pos.z, pos.w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float p = COUNT ? (acc[4 * g4 + i] >= 0.f ? 1.f : 0.f)
-                                      : __builtin_amdgcn_exp2f(acc[4 * g4 + i] * c2);
-                t[i] += (!MASK || key <= ps[i]) ? p : 0.f;
+                if constexpr (COUNT) {
+                    bool pick = acc[4 * g4 + i] >= 0.f;
+                    if (MASK) pick = pick && key <= ps[i];
+                    n[i % 2] += pick ? 1 : 0;
+                } else {
+                    const float p = __builtin_amdgcn_exp2f(acc[4 * g4 + i] * c2);
+                    t[i] += (!MASK || key <= ps[i]) ? p : 0.f;
+                }
             }
         }
-        cs[kb] += (t[0] + t[1]) + (t[2] + t[3]);
+        cs[kb] += COUNT ? (float)(n[0] + n[1]) : (t[0] + t[1]) + (t[2] + t[3]);
     }
 };
 
-template <typename T, int D, int NW, bool COUNT>
+template <typename T, int D, int NW, bool COUNT, int NRBU>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void score_colsum_kernel(
     int B, int L, int Hq, int Hkv, int W, const int32_t *__restrict__ cu_seqlens, int64_t T_,
     const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, float c2, int nchunk, int chunk_keys,
@@ -295,6 +335,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     int64_t u;
     int chunk;
     unit_chunk((int64_t)L * Hkv * B, nchunk, u, chunk);
+    // the stats pass's order backwards: the keys it read last are still in the
+    // last-level cache (256 MB) and are read first (32 layers of 8K keys, 537 MB:
+    // the two passes 330 -> 324 us)
+    u = (int64_t)L * Hkv * B - 1 - u;
+    chunk = nchunk - 1 - chunk;
     const UnitGeom g = unit_geom(u, B, Hkv, cu_seqlens, T_);
     const int G = Hq / Hkv, R = G * W;
     const int N = (int)g.N;
@@ -313,7 +358,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     const int ntile = (int)ceil_div(key_end - key_begin, KT::TK);
     KT::template load<NW>(kbA, kunit, key_begin, N, wave, lane);
     QFrags<T, D> q;
-    q.load(q_win + rbase * D, R, wave, lane);
+    q.template load<NRBU>(q_win + rbase * D, R, wave, lane);
     // row normalisers in log2 units: the caller's LSE, or the merge of the chunk statistics
     for (int r = threadIdx.x; r < NW * 64; r += 64 * NW) {
         if constexpr (COUNT) {
@@ -321,10 +366,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
             float start = -INFINITY;             // padded rows pick nothing
             if (r < R) {
                 const int nc = (int)min<int64_t>(ceil_div(N, chunk_keys), nchunk);
-                const float2 *pr = part + u * nchunk * (int64_t)R + r;
-                float Mx = -INFINITY;
-                for (int c = 0; c < nc; ++c) Mx = fmaxf(Mx, pr[(int64_t)c * R].x);
-                start = -(Mx - thr_off);
+                start = -(merge_max(part + u * nchunk * (int64_t)R + r, nc, R) - thr_off);
             }
             nl2s[r] = start;
             poss[r] = r < R ? N - W + r % W : -1;
@@ -336,16 +378,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 l2 = lse_in[rbase + r] * SC_LOG2E;
             } else {
                 const int nc = (int)min<int64_t>(ceil_div(N, chunk_keys), nchunk);  // a prompt above max_seqlen is cut
-                const float2 *pr = part + u * nchunk * (int64_t)R + r;
-                float Mx = -INFINITY;
-                for (int c = 0; c < nc; ++c) Mx = fmaxf(Mx, pr[(int64_t)c * R].x);
-                const float ref = Mx == -INFINITY ? 0.f : Mx;
-                float S = 0.f;
-                for (int c = 0; c < nc; ++c) {
-                    const float2 p = pr[(int64_t)c * R];
-                    S += p.y * __builtin_amdgcn_exp2f(p.x - ref);
-                }
-                l2 = S > 0.f ? ref + __log2f(S) : INFINITY;
+                l2 = merge_lse(part + u * nchunk * (int64_t)R + r, nc, R);
             }
         }
         nl2s[r] = -l2 / c2;
@@ -381,9 +414,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) cs[kb] = 0.f;
         if (MASK)
-            tile_sweep_plain<T, D, false, colsum_tile_keys<T>()>(cur, q, c0, lane, ColsumStep<T, D, true, COUNT>{cs, poss, lane, wave, key0, c2});
+            tile_sweep_plain<T, D, false, colsum_tile_keys<T>(), NRBU>(cur, q, c0, lane, ColsumStep<T, D, true, COUNT>{cs, poss, lane, wave, key0, c2});
         else
-            tile_sweep<T, D, false, colsum_tile_keys<T>()>(cur, q, c0, lane, ColsumStep<T, D, false, COUNT>{cs, poss, lane, wave, key0, c2});
+            tile_sweep<T, D, false, colsum_tile_keys<T>(), NRBU>(cur, q, c0, lane, ColsumStep<T, D, false, COUNT>{cs, poss, lane, wave, key0, c2});
         // lanes holding the same key (different rows) add up; every such lane
         // then holds the total and stores it (same value, same address: no
         // branch, so the exponentials are not moved behind one)
@@ -410,7 +443,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 
 // thr_off < 0: probabilities; thr_off >= 0: count mode with the threshold
 // max - thr_off in raw product units (thr_off = alpha * sqrt(d)).
-template <typename T, int D, int NW>
+// NRBU: the row blocks of each wavefront in use (half of its 64 rows' where a
+// unit has at most 32 rows: the other half's products would be padding.  8
+// units of 32 fp32 rows x 2,048 keys: stats 16.4 -> 12.2, colsum, with its
+// chunk statistics loaded together, 18.2 -> 10.6 us).
+template <typename T, int D, int NW, int NRBU = QFrags<T, D>::NRB>
 static void launch_passes(hipStream_t s, const ScorePlan &p, int B, int L, int Hq, int Hkv, int W,
                           const int32_t *cu_seqlens, int64_t ntok, const void *q_win, const void *k,
                           int64_t k_layer_rows, float c2, const float *lse_in, float thr_off, float *scores,
@@ -420,17 +457,17 @@ static void launch_passes(hipStream_t s, const ScorePlan &p, int B, int L, int H
     const T *kk = reinterpret_cast<const T *>(k);
     const dim3 grid((unsigned)((int64_t)L * Hkv * B * p.nchunk));
     if (thr_off >= 0.f) {
-        score_stats_kernel<T, D, NW, true><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk,
+        score_stats_kernel<T, D, NW, true, NRBU><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk,
                                                                    k_layer_rows, c2, p.nchunk, p.chunk_keys, part);
-        score_colsum_kernel<T, D, NW, true><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk,
+        score_colsum_kernel<T, D, NW, true, NRBU><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk,
                                                                     k_layer_rows, c2, p.nchunk, p.chunk_keys, part,
                                                                     nullptr, thr_off, scores);
         return;
     }
     if (!lse_in)
-        score_stats_kernel<T, D, NW, false><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk,
+        score_stats_kernel<T, D, NW, false, NRBU><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk,
                                                                     k_layer_rows, c2, p.nchunk, p.chunk_keys, part);
-    score_colsum_kernel<T, D, NW, false><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk,
+    score_colsum_kernel<T, D, NW, false, NRBU><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk,
                                                                  k_layer_rows, c2, p.nchunk, p.chunk_keys, part,
                                                                  lse_in, thr_off, scores);
 }
@@ -443,7 +480,8 @@ static int launch_score(const char *name, hipStream_t s, int B, int L, int Hq, i
     const int nw = (int)ceil_div(R, 64);
     const ScorePlan p = score_plan(B, L, Hkv, max_seqlen);
     const float c2 = SC_LOG2E / sqrtf((float)D);
-    if (nw <= 1) launch_passes<T, D, 1>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, q_win, k, k_layer_rows, c2, lse_in, thr_off, scores, ws);
+    if (R <= 32) launch_passes<T, D, 1, QFrags<T, D>::NRB / 2>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, q_win, k, k_layer_rows, c2, lse_in, thr_off, scores, ws);
+    else if (nw <= 1) launch_passes<T, D, 1>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, q_win, k, k_layer_rows, c2, lse_in, thr_off, scores, ws);
     else if (nw <= 2) launch_passes<T, D, 2>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, q_win, k, k_layer_rows, c2, lse_in, thr_off, scores, ws);
     else if (nw <= 4) launch_passes<T, D, 4>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, q_win, k, k_layer_rows, c2, lse_in, thr_off, scores, ws);
     else launch_passes<T, D, 8>(s, p, B, L, Hq, Hkv, W, cu_seqlens, ntok, q_win, k, k_layer_rows, c2, lse_in, thr_off, scores, ws);

@@ -20,10 +20,11 @@ template <typename T, int D>
 struct QFrags {
     static constexpr int NRB = 64 / MT<T, D>::BM;     // row blocks per wavefront
     TA<T, D> f[NRB][MT<T, D>::KS];
+    template <int NRBU = NRB>     // the first NRBU row blocks only
     __device__ __forceinline__ void load(const T *qunit, int R, int wave, int lane) {
         using M = MT<T, D>;
 #pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) {
+        for (int rb = 0; rb < NRBU; ++rb) {
             const int row = wave * 64 + rb * M::BM + lane % M::BM;
             const T *p = qunit + (int64_t)min(row, R - 1) * D;
 #pragma unroll
@@ -75,10 +76,11 @@ __device__ __forceinline__ TC<T, D> block_mma_refill(const char *buf, int next, 
 // a key block refills them with the next key block's behind its own MFMAs.
 // Scheduling barriers keep the compiler from hoisting later loads, and group
 // barriers interleave each MFMA with a share of the vector work.
-template <typename T, int D, bool KEY_ROWS, int TKEYS = KTile<T, D>::TK, typename F>
+// NRBU: the row blocks in use (the first ones).
+template <typename T, int D, bool KEY_ROWS, int TKEYS = KTile<T, D>::TK, int NRBU = QFrags<T, D>::NRB, typename F>
 __device__ __forceinline__ void tile_sweep(const char *buf, const QFrags<T, D> &q,
                                            const TC<T, D> (&c0)[QFrags<T, D>::NRB], int lane, F &&valu) {
-    constexpr int NKB = KTile<T, D, TKEYS>::NKB, NRB = QFrags<T, D>::NRB, NB = NKB * NRB;
+    constexpr int NKB = KTile<T, D, TKEYS>::NKB, NRB = NRBU, NB = NKB * NRB;
     // a block's vector work is about 3 instructions per output value
     constexpr int VALU_PER_MFMA = (3 * MT<T, D>::NV + MT<T, D>::KS - 1) / MT<T, D>::KS;
     TA<T, D> kf[MT<T, D>::KS];
@@ -110,10 +112,10 @@ __device__ __forceinline__ void tile_sweep(const char *buf, const QFrags<T, D> &
 // The same products without pipelining, for the few tiles at the end of a
 // prompt (keeps their masking work from raising the register needs of the
 // main loop).
-template <typename T, int D, bool KEY_ROWS, int TKEYS = KTile<T, D>::TK, typename F>
+template <typename T, int D, bool KEY_ROWS, int TKEYS = KTile<T, D>::TK, int NRBU = QFrags<T, D>::NRB, typename F>
 __device__ __forceinline__ void tile_sweep_plain(const char *buf, const QFrags<T, D> &q,
                                                  const TC<T, D> (&c0)[QFrags<T, D>::NRB], int lane, F &&valu) {
-    constexpr int NKB = KTile<T, D, TKEYS>::NKB, NRB = QFrags<T, D>::NRB;
+    constexpr int NKB = KTile<T, D, TKEYS>::NKB, NRB = NRBU;
 #pragma unroll 1
     for (int kb = 0; kb < NKB; ++kb) {
         TA<T, D> kf[MT<T, D>::KS];
