@@ -8,8 +8,11 @@ lanes fill the decode pool at once:
   - the remote lane (sg_fetch_keep, or sg_fetch without reuse) fetches the
     remote entries from the prefill side's copy into pool rows [0, n_remote),
     and with reuse keeps them in the store and marks them local.
-Each lane runs on its own stream; the caller's stream waits for both, so the
-attention that follows on it sees the whole pool.
+The remote lane, the longer one, runs on the caller's stream right behind the
+split, the local lane beside it on a stream of its own; the caller's stream then
+waits for the local lane, so the attention that follows on it sees the whole
+pool.  (A second stream for the remote lane adds two waits across streams to
+every step.)
 
 SpecPusher sends the blocks that the proactive transfer left behind, a quota at
 a time in importance order, on a side stream, without holding up any decode
@@ -47,11 +50,10 @@ class StepBuffers:
 
 
 class TwoLane:
-    """Streams and events of the two lanes; create once, reuse every step."""
+    """The local lane's stream; create once, reuse every step."""
 
     def __init__(self, device=None):
         self.local_stream = torch.cuda.Stream(device=device)
-        self.remote_stream = torch.cuda.Stream(device=device)
 
     def gather(self, *, row_off, kv_index, mask, mask_off, mask_len, store_k, store_v, store_base, src_k, src_v,
                src_base, page_table, page_size, k_pool, v_pool, buf: StepBuffers, reuse=True, stream=None):
@@ -67,21 +69,18 @@ class TwoLane:
         split_done = torch.cuda.Event()
         split_done.record(main)
         self.local_stream.wait_event(split_done)
-        self.remote_stream.wait_event(split_done)
         sg.sg_fetch(row_off, total, buf.local, buf.n_local, store_base, store_k, store_v, page_table, page_size,
                     buf.n_remote, k_pool, v_pool, stream=self.local_stream)
         if reuse:
             sg.sg_fetch_keep(row_off, total, buf.remote, buf.n_remote, src_base, src_k, src_v, page_table, page_size,
                              buf.zeros, k_pool, v_pool, store_base, store_k, store_v, mask, mask_off, mask_len,
-                             stream=self.remote_stream)
+                             stream=main)
         else:
             sg.sg_fetch(row_off, total, buf.remote, buf.n_remote, src_base, src_k, src_v, page_table, page_size,
-                        buf.zeros, k_pool, v_pool, stream=self.remote_stream)
-        done_l, done_r = torch.cuda.Event(), torch.cuda.Event()
-        done_l.record(self.local_stream)
-        done_r.record(self.remote_stream)
-        main.wait_event(done_l)
-        main.wait_event(done_r)
+                        buf.zeros, k_pool, v_pool, stream=main)
+        done = torch.cuda.Event()
+        done.record(self.local_stream)
+        main.wait_event(done)
         return buf.n_kept
 
 
