@@ -9,8 +9,8 @@
 //   +inf, empty blocks -inf.
 // sg_pack_blocks: a selected block moves Hkv * Nb contiguous source rows per
 //   tensor; the grid is flat over 16-byte vectors of the output, each thread
-//   issues the loads of all its vectors before any store (non-temporal), so
-//   the copy runs like a plain strided memcpy.
+//   issues the loads of its vectors before any store (non-temporal), so the
+//   copy runs like a plain strided memcpy.
 // sg_spec_push (speculative transfer, Section 4.3): the same flat copy, with
 //   each row stored at its own position in the decode side's store, its mask
 //   entry turned local and the block marked in the remaining importances
@@ -73,48 +73,58 @@ __global__ __launch_bounds__(BLK_THREADS) void block_importance_kernel(int B, in
 
 constexpr int PB_UNROLL = 4;
 
+// Block pack: one wavefront per workgroup, two vectors per thread and tensor.
+// Bound by HBM (1.28 GB moved, blocks of 32 rows x 8 heads of 256 B): 208-211
+// us, 77% of 8 TB/s; 256 threads with four vectors 224, with two 226, with one
+// 232; 64 threads with one 226, three 218, four 220; 128 with one 226.
+constexpr int PK_THREADS = 64;
+constexpr int PK_UNROLL = 2;
+
 // Output vector i of the K (or V) region: slot row r_all = i / CPR, vector
-// c = i % CPR; slot row r_all = (s * Hkv + h) * Nb + r.
-template <int CPR>
-__global__ __launch_bounds__(BLK_THREADS) void pack_blocks_kernel(int L, int Hkv, int64_t T, int64_t s0, int64_t N,
-                                                                    int M, int64_t Nb, const v4u *__restrict__ k,
-                                                                    const v4u *__restrict__ v, int64_t kv_layer_rows,
-                                                                    int nblk, const int32_t *__restrict__ ids,
-                                                                    v4u *__restrict__ dk, v4u *__restrict__ dv,
-                                                                    int32_t *__restrict__ did) {
-    const int64_t total = (int64_t)nblk * Hkv * Nb * CPR;
-    const int64_t stride = (int64_t)gridDim.x * BLK_THREADS * PB_UNROLL;
-    for (int64_t base = (int64_t)blockIdx.x * BLK_THREADS * PB_UNROLL + threadIdx.x; base < total; base += stride) {
-        v4u kr[PB_UNROLL], vr[PB_UNROLL];
-        bool ok[PB_UNROLL];
+// c = i % CPR; slot row r_all = (s * Hkv + h) * Nb + r.  I: the index type (32
+// bits while the vectors number below 2^31: the divisions by run-time sizes are
+// a good part of a 64-bit thread's instructions).
+template <int CPR, typename I>
+__global__ __launch_bounds__(PK_THREADS) void pack_blocks_kernel(int L, int Hkv, int64_t T, int64_t s0, int64_t N,
+                                                                   int M, int64_t Nb_, const v4u *__restrict__ k,
+                                                                   const v4u *__restrict__ v, int64_t kv_layer_rows,
+                                                                   int nblk, const int32_t *__restrict__ ids,
+                                                                   v4u *__restrict__ dk, v4u *__restrict__ dv,
+                                                                   int32_t *__restrict__ did) {
+    const I Nb = (I)Nb_, total = (I)nblk * (I)Hkv * Nb * CPR;
+    const int64_t stride = (int64_t)gridDim.x * PK_THREADS * PK_UNROLL;
+    for (int64_t base = (int64_t)blockIdx.x * PK_THREADS * PK_UNROLL + threadIdx.x; base < (int64_t)total;
+         base += stride) {
+        v4u kr[PK_UNROLL], vr[PK_UNROLL];
+        bool ok[PK_UNROLL];
         // every load of the pass first (a row past the prompt or of an invalid
         // id reads the request's first row and is zeroed)
 #pragma unroll
-        for (int u = 0; u < PB_UNROLL; ++u) {
-            const int64_t i = min(base + (int64_t)u * BLK_THREADS, total - 1);
-            const int64_t row = i / CPR, c = i % CPR;
-            const int64_t r = row % Nb, sh = row / Nb;
-            const int h = (int)(sh % Hkv), s = (int)(sh / Hkv);
+        for (int u = 0; u < PK_UNROLL; ++u) {
+            const I i = (I)min<int64_t>(base + (int64_t)u * PK_THREADS, (int64_t)total - 1);
+            const I row = i / CPR, c = i % CPR;
+            const I sh = row / Nb, r = row - sh * Nb;
+            const I s = sh / (I)Hkv, h = sh - s * (I)Hkv;
             const int32_t id = ids[s];
             const bool valid = id >= 0 && (int64_t)id < (int64_t)L * M;
-            const int l = valid ? id / M : 0, m = valid ? id % M : 0;
-            const int64_t t = (int64_t)m * Nb + r;
+            const int l = valid ? id / M : 0, m = valid ? id - l * M : 0;
+            const int64_t t = (int64_t)m * Nb_ + (int64_t)r;
             ok[u] = valid && t < N;
-            const int64_t src = ((int64_t)l * kv_layer_rows + (int64_t)h * T + s0 + (ok[u] ? t : 0)) * CPR + c;
+            const int64_t src = ((int64_t)l * kv_layer_rows + (int64_t)h * T + s0 + (ok[u] ? t : 0)) * CPR + (int64_t)c;
             kr[u] = __builtin_nontemporal_load(k + src);
             vr[u] = __builtin_nontemporal_load(v + src);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < PB_UNROLL; ++u) {
-            const int64_t i = base + (int64_t)u * BLK_THREADS;
-            if (i < total) {
+        for (int u = 0; u < PK_UNROLL; ++u) {
+            const int64_t i = base + (int64_t)u * PK_THREADS;
+            if (i < (int64_t)total) {
                 __builtin_nontemporal_store(ok[u] ? kr[u] : v4u{0u, 0u, 0u, 0u}, dk + i);
                 __builtin_nontemporal_store(ok[u] ? vr[u] : v4u{0u, 0u, 0u, 0u}, dv + i);
             }
         }
     }
-    for (int64_t s = (int64_t)blockIdx.x * BLK_THREADS + threadIdx.x; s < nblk; s += (int64_t)gridDim.x * BLK_THREADS)
+    for (int64_t s = (int64_t)blockIdx.x * PK_THREADS + threadIdx.x; s < nblk; s += (int64_t)gridDim.x * PK_THREADS)
         did[s] = ids[s];
 }
 
@@ -253,16 +263,21 @@ extern "C" int sg_pack_blocks(void *stream, sg_dtype dt, int L, int Hkv, int d, 
     v4u *dv = dk + S * cpr;
     int32_t *di = reinterpret_cast<int32_t *>(dv + S * cpr);
     const int64_t total = S * cpr;
-    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(total, BLK_THREADS * PB_UNROLL), 65536));
+    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(total, PK_THREADS * PK_UNROLL), 0x7fffffff));
     hipStream_t s = as_stream(stream);
     const v4u *kk = reinterpret_cast<const v4u *>(k);
     const v4u *vv = reinterpret_cast<const v4u *>(v);
+    const bool small = total <= 0x7fffffff;
+#define SG_PACK_BLOCKS(C, I)                                                                                       \
+    pack_blocks_kernel<C, I><<<(unsigned)grid, PK_THREADS, 0, s>>>(L, Hkv, T, s0, N, M, Nb, kk, vv, kv_layer_rows, \
+                                                                   nblk, ids, dk, dv, di)
     switch (cpr) {
-        case 8: pack_blocks_kernel<8><<<(unsigned)grid, BLK_THREADS, 0, s>>>(L, Hkv, T, s0, N, M, Nb, kk, vv, kv_layer_rows, nblk, ids, dk, dv, di); break;
-        case 16: pack_blocks_kernel<16><<<(unsigned)grid, BLK_THREADS, 0, s>>>(L, Hkv, T, s0, N, M, Nb, kk, vv, kv_layer_rows, nblk, ids, dk, dv, di); break;
-        case 32: pack_blocks_kernel<32><<<(unsigned)grid, BLK_THREADS, 0, s>>>(L, Hkv, T, s0, N, M, Nb, kk, vv, kv_layer_rows, nblk, ids, dk, dv, di); break;
+        case 8: if (small) SG_PACK_BLOCKS(8, uint32_t); else SG_PACK_BLOCKS(8, uint64_t); break;
+        case 16: if (small) SG_PACK_BLOCKS(16, uint32_t); else SG_PACK_BLOCKS(16, uint64_t); break;
+        case 32: if (small) SG_PACK_BLOCKS(32, uint32_t); else SG_PACK_BLOCKS(32, uint64_t); break;
         default: set_error("sg_pack_blocks: internal row size"); return SG_EINTERNAL;
     }
+#undef SG_PACK_BLOCKS
     return launch_status("sg_pack_blocks");
 }
 
