@@ -24,10 +24,10 @@ CFLAGS = [
     "-I", os.path.join(_ROOT, "include"),
 ]
 
-# Per-file additions.  topshare.hip: its histogram kernels hold 130 KB of LDS,
-# so one workgroup per CU and a register budget above 256, where the compiler
-# would put the MFMA accumulators in AGPRs and copy every value out before the
-# vector work; the VGPR form fits the bf16 kernels in 256 VGPRs without spills.
+# Per-file additions.  topshare.hip: its kernels run at one or two wavefronts
+# per SIMD, a register budget above 256 where the compiler may put the MFMA
+# accumulators in AGPRs and copy every value out before the vector work; the
+# VGPR form fits the bf16 kernels in 256 VGPRs without spills.
 FILE_FLAGS = {
     "topshare.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
