@@ -1,0 +1,21 @@
+// Launch arithmetic.  Nothing here needs HIP, so the host tests compile this
+// file by itself.
+#pragma once
+
+#include <stdint.h>
+
+namespace sg {
+
+// Workgroups of `threads` threads that one grid dimension may hold: its
+// threads are counted in 32 bits (a larger launch is refused).
+constexpr int64_t max_workgroups(int64_t threads) { return 0xffffffffll / threads; }
+
+// Workgroups of a grid-stride kernel over `total` items, `per` items per
+// workgroup and pass: one pass where the launch may be that large, else the
+// kernel's stride loop takes the rest.
+constexpr int64_t stride_grid(int64_t total, int64_t per, int threads) {
+    const int64_t need = (total + per - 1) / per, most = max_workgroups(threads);
+    return need < 1 ? 1 : need < most ? need : most;
+}
+
+}  // namespace sg

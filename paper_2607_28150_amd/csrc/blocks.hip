@@ -263,7 +263,7 @@ extern "C" int sg_pack_blocks(void *stream, sg_dtype dt, int L, int Hkv, int d, 
     v4u *dv = dk + S * cpr;
     int32_t *di = reinterpret_cast<int32_t *>(dv + S * cpr);
     const int64_t total = S * cpr;
-    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(total, PK_THREADS * PK_UNROLL), 0x7fffffff));
+    const int64_t grid = stride_grid(total, PK_THREADS * PK_UNROLL, PK_THREADS);
     hipStream_t s = as_stream(stream);
     const v4u *kk = reinterpret_cast<const v4u *>(k);
     const v4u *vv = reinterpret_cast<const v4u *>(v);

@@ -5,6 +5,7 @@
 #include <stdarg.h>
 #include <stdint.h>
 
+#include "arith.h"
 #include "smartgen.h"
 
 namespace sg {

@@ -140,3 +140,30 @@ def test_block_mode_llama8b_8k(gpu_lib):
     torch.cuda.synchronize()
     ref_buf = oracle.pack_blocks(raw(pre["k"]), raw(pre["v"]), ref_ids[0, 0], 0, N, M)
     np.testing.assert_array_equal(dst.cpu().numpy(), ref_buf)
+
+
+@pytest.mark.parametrize("nblk", [4095, 4097])
+def test_pack_blocks_either_side_of_32_bit_vectors(gpu_lib, nblk):
+    """The 32- and the 64-bit index form of the pack, either side of 2^31 16-byte
+    vectors per tensor: 8 heads x 2,048 rows of 512 B per block, the blocks drawn
+    from a source of 16."""
+    L, Hkv, d, Nb, M = 2, 8, 128, 2048, 8
+    N = Nb * M
+    nbytes = gpu_lib.pack_blocks_bytes(torch.float32, Hkv, d, N, M, nblk)
+    say("pack blocks of", nbytes, "bytes")
+    if torch.cuda.mem_get_info()[0] < nbytes + (8 << 30):
+        pytest.skip("not enough free device memory")
+    g = torch.Generator(device="cuda").manual_seed(nblk)
+    k, v = (torch.randn((L, Hkv, N, d), generator=g, device="cuda") for _ in range(2))
+    ids = torch.randint(0, L * M, (nblk,), generator=g, device="cuda", dtype=torch.int32)
+    dst = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    gpu_lib.sg_pack_blocks(k, v, ids, 0, N, M, dst)
+    n = nblk * Hkv * Nb * d * 4
+    assert torch.equal(dst[2 * n:].view(torch.int32), ids)
+    for i, src in enumerate((k, v)):
+        got = dst[i * n:(i + 1) * n].view(torch.float32).view(nblk, Hkv, Nb, d)
+        blocks = src.view(L, Hkv, M, Nb, d).transpose(1, 2).reshape(L * M, Hkv, Nb, d)
+        for s in range(0, nblk, 256):
+            assert torch.equal(got[s:s + 256], blocks[ids[s:s + 256].long()]), (i, s)
+    del dst, got
+    torch.cuda.empty_cache()
