@@ -18,4 +18,13 @@ constexpr int64_t stride_grid(int64_t total, int64_t per, int threads) {
     return need < 1 ? 1 : need < most ? need : most;
 }
 
+// launch(first, n) for the pieces [first, first + n) of `count` that one launch
+// of `threads` threads each may hold.
+template <typename F>
+void launch_slices(int64_t count, int64_t threads, F &&launch) {
+    const int64_t most = max_workgroups(threads);
+    for (int64_t first = 0; first < count; first += most)
+        launch(first, count - first < most ? count - first : most);
+}
+
 }  // namespace sg

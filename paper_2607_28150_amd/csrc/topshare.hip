@@ -123,7 +123,7 @@ __device__ __forceinline__ int64_t ts_rank(int64_t n, int ratio_bp) {
 template <typename T, int D, int NWV, int ROWS>
 __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) void ts_sample_kernel(
     int B, int L, int Hq, int Hkv, int W, const int32_t *__restrict__ cu_seqlens, int64_t T_,
-    const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int ratio_bp, TsWork ws) {
+    const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int ratio_bp, int64_t u0, TsWork ws) {
     using M = MT<T, D>;
     constexpr int NRB = ROWS / M::BM, SPW = 8192 / ROWS, NKB = SPW / M::BM, NS = SPW * NWV;
     constexpr int SB = 128, QB = SB / 4;       // bins of the sample; a quarter of them
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
     __shared__ float smin[NWV][ROWS], smax[NWV][ROWS], ra[ROWS], rs[ROWS];
     __shared__ int qsum[4][ROWS], found[4][ROWS];  // found: the bins of the two ranks and the samples above them
     const int R = (Hq / Hkv) * W, ngrp = (int)ceil_div(R, ROWS);
-    const int64_t u = blockIdx.x / ngrp;
+    const int64_t u = u0 + blockIdx.x / ngrp;
     const int grp = blockIdx.x % ngrp;
     const UnitGeom g = unit_geom(u, B, Hkv, cu_seqlens, T_);
     const int N = (int)g.N, tid = threadIdx.x, lane = tid % 64;
@@ -649,9 +649,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 // list cut short (more matches in one chunk than a lane's list holds) sends
 // the row to the radix select.
 constexpr int PICK_ROWS = 8;
-__global__ __launch_bounds__(256) void ts_pick_kernel(int64_t nrows, int R, TsWork ws) {
+__global__ __launch_bounds__(256) void ts_pick_kernel(int64_t nrows, int R, int64_t group0, TsWork ws) {
     const int lane = threadIdx.x % 64;
-    const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int64_t wave = (group0 + blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const int64_t i0 = wave * PICK_ROWS;
     if (i0 >= nrows) return;
     const int64_t mine = min(i0 + lane % PICK_ROWS, nrows - 1);
@@ -716,7 +716,7 @@ constexpr int TS_RADIX_WAVES = 8, TS_RADIX_COPIES = 2;
 template <typename T, int D>
 __global__ __launch_bounds__(64 * TS_RADIX_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void ts_radix_kernel(
     int B, int L, int Hq, int Hkv, int W, const int32_t *__restrict__ cu_seqlens, int64_t T_,
-    const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int ratio_bp, TsWork ws) {
+    const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int ratio_bp, int64_t u0, TsWork ws) {
     using M = MT<T, D>;
     constexpr int NB32 = 32 / M::BM;                   // row blocks
     using KT = KTile<T, D, M::BM>;                     // one key block
@@ -729,7 +729,7 @@ __global__ __launch_bounds__(64 * TS_RADIX_WAVES) __attribute__((amdgpu_waves_pe
     __shared__ int64_t rank[32];
     __shared__ int bits;
     const int R = (Hq / Hkv) * W, ngrp = (int)ceil_div(R, 32);
-    const int64_t u = blockIdx.x / ngrp;
+    const int64_t u = u0 + blockIdx.x / ngrp;
     const int grp = blockIdx.x % ngrp;
     if (((ws.fail[u] >> grp) & 1u) == 0u) return;
     const UnitGeom g = unit_geom(u, B, Hkv, cu_seqlens, T_);
@@ -988,9 +988,13 @@ static void launch_topshare(hipStream_t s, const ScorePlan &p, int B, int L, int
     const dim3 grid((unsigned)(units * p.nchunk));
     // a larger sample for longer prompts: the interval, and so a bin, then holds
     // about as many keys (8K keys: about 22 of the 92 a row may gather; 32K: 45)
+    // (sample, radix and pick have more threads per unit than the others: calls
+    // of some million units take more than one launch of them)
 #define SG_SAMPLE(NWV, ROWS)                                                                            \
-    ts_sample_kernel<T, D, NWV, ROWS><<<(unsigned)(units * ceil_div(R, ROWS)), 64 * NWV, 0, s>>>(        \
-        B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows, ratio_bp, ws)
+    launch_slices(units, ceil_div(R, ROWS) * 64 * NWV, [&](int64_t u0, int64_t n) {                      \
+        ts_sample_kernel<T, D, NWV, ROWS><<<(unsigned)(n * ceil_div(R, ROWS)), 64 * NWV, 0, s>>>(        \
+            B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows, ratio_bp, u0, ws);                  \
+    })
     if (max_seqlen <= 12288) SG_SAMPLE(4, 64);             // 512 keys
     else if (max_seqlen <= 24576) SG_SAMPLE(8, 64);        // 1024
     else SG_SAMPLE(8, 32);                                 // 2048
@@ -1004,9 +1008,13 @@ static void launch_topshare(hipStream_t s, const ScorePlan &p, int B, int L, int
     ts_digit_kernel<true><<<dgrid, TS_DIGIT_THREADS, 0, s>>>(R, W, B, Hkv, cu_seqlens, ntok, ratio_bp, ws);
     ts_gather_kernel<T, D, NW><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows,
                                                         p.nchunk, p.chunk_keys, ws);
-    ts_pick_kernel<<<(unsigned)ceil_div(nrows, 4 * PICK_ROWS), 256, 0, s>>>(nrows, R, ws);
-    ts_radix_kernel<T, D><<<(unsigned)(units * ceil_div(R, 32)), 64 * TS_RADIX_WAVES, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q,
-                                                                             kk, k_layer_rows, ratio_bp, ws);
+    launch_slices(ceil_div(nrows, 4 * PICK_ROWS), 256, [&](int64_t group0, int64_t n) {
+        ts_pick_kernel<<<(unsigned)n, 256, 0, s>>>(nrows, R, group0, ws);
+    });
+    launch_slices(units, ceil_div(R, 32) * 64 * TS_RADIX_WAVES, [&](int64_t u0, int64_t n) {
+        ts_radix_kernel<T, D><<<(unsigned)(n * ceil_div(R, 32)), 64 * TS_RADIX_WAVES, 0, s>>>(
+            B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows, ratio_bp, u0, ws);
+    });
     ts_count_kernel<T, D, NW><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows,
                                                       p.nchunk, p.chunk_keys, ws.thr, counts);
 }

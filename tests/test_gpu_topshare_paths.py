@@ -41,3 +41,23 @@ def test_topshare_paths_exact(gpu_lib, dtype, G, W, d, lens, bp, kind):
     got, cus = _topshare(gpu_lib, q, k, lens, Hkv, bp)
     ref = oracle.score_topshare(q.float().numpy(), k.float().numpy(), cus, Hkv, bp)
     np.testing.assert_array_equal(got, ref.astype(np.float32))
+
+
+def test_topshare_many_units(gpu_lib):
+    """8,388,672 units of one row and two keys: more threads than one launch of
+    some passes may hold.  Integer logits, so the larger one (both, if they tie)
+    is picked exactly."""
+    B, L, d, N = 131073, 64, 64, 2
+    say("topshare many units", B, L)
+    T = B * N
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q = torch.randint(-3, 4, (B, L, 1, 1, d), generator=g, device="cuda", dtype=torch.int8).to(torch.bfloat16)
+    k = torch.randint(-3, 4, (L, 1, T, d), generator=g, device="cuda", dtype=torch.int8).to(torch.bfloat16)
+    cus = torch.arange(0, T + 1, N, dtype=torch.int32, device="cuda")
+    ws = torch.full((gpu_lib.score_topshare_workspace_size(B, L, 1, 1, d, 1, N),), 0xA5, dtype=torch.uint8,
+                    device="cuda")
+    out = torch.full((L, 1, T), -1.0, device="cuda")
+    gpu_lib.sg_score_topshare(q, k, cus, T, N, 1, out, 5000, ws)
+    for l in range(L):
+        z = (q[:, l, 0].float() * k[l, 0].view(B, N, d).float()).sum(-1)
+        assert torch.equal(out[l, 0].view(B, N), (z >= z.amax(1, keepdim=True)).float()), l
