@@ -12,7 +12,7 @@ The remote lane, the longer one, runs on the caller's stream right behind the
 split, the local lane beside it on a stream of its own; the caller's stream then
 waits for the local lane, so the attention that follows on it sees the whole
 pool.  (A second stream for the remote lane adds two waits across streams to
-every step.)
+every step; a caller that asks for one, to order its own work on it, gets it.)
 
 SpecPusher sends the blocks that the proactive transfer left behind, a quota at
 a time in importance order, on a side stream, without holding up any decode
@@ -50,10 +50,19 @@ class StepBuffers:
 
 
 class TwoLane:
-    """The local lane's stream; create once, reuse every step."""
+    """Streams of the two lanes; create once, reuse every step."""
 
     def __init__(self, device=None):
         self.local_stream = torch.cuda.Stream(device=device)
+        self._remote_stream = None
+
+    @property
+    def remote_stream(self):
+        """The remote lane's own stream, made when it is first asked for: from
+        then on the remote lane runs on it, behind what the caller put there."""
+        if self._remote_stream is None:
+            self._remote_stream = torch.cuda.Stream(device=self.local_stream.device)
+        return self._remote_stream
 
     def gather(self, *, row_off, kv_index, mask, mask_off, mask_len, store_k, store_v, store_base, src_k, src_v,
                src_base, page_table, page_size, k_pool, v_pool, buf: StepBuffers, reuse=True, stream=None):
@@ -69,18 +78,25 @@ class TwoLane:
         split_done = torch.cuda.Event()
         split_done.record(main)
         self.local_stream.wait_event(split_done)
+        lanes = [self.local_stream]
+        remote = main
+        if self._remote_stream is not None:
+            remote = self._remote_stream
+            remote.wait_event(split_done)
+            lanes.append(remote)
         sg.sg_fetch(row_off, total, buf.local, buf.n_local, store_base, store_k, store_v, page_table, page_size,
                     buf.n_remote, k_pool, v_pool, stream=self.local_stream)
         if reuse:
             sg.sg_fetch_keep(row_off, total, buf.remote, buf.n_remote, src_base, src_k, src_v, page_table, page_size,
                              buf.zeros, k_pool, v_pool, store_base, store_k, store_v, mask, mask_off, mask_len,
-                             stream=main)
+                             stream=remote)
         else:
             sg.sg_fetch(row_off, total, buf.remote, buf.n_remote, src_base, src_k, src_v, page_table, page_size,
-                        buf.zeros, k_pool, v_pool, stream=main)
-        done = torch.cuda.Event()
-        done.record(self.local_stream)
-        main.wait_event(done)
+                        buf.zeros, k_pool, v_pool, stream=remote)
+        for lane in lanes:
+            done = torch.cuda.Event()
+            done.record(lane)
+            main.wait_event(done)
         return buf.n_kept
 
 

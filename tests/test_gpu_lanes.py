@@ -201,3 +201,41 @@ def test_dynamic_decode_steps_exact(gpu_lib):
         ratios.append(r_nr.sum() / (r_nl + r_nr).sum())
     np.testing.assert_array_equal(raw(store_k).reshape(-1, d), o_sk)
     assert ratios[0] > 0 and ratios[-1] <= ratios[0]      # reuse: fetched rows turn local
+
+
+@pytest.mark.parametrize("asked", [True, False])
+def test_two_lane_work_ordered_on_the_remote_stream(gpu_lib, asked):
+    """What a caller puts on the remote lane's stream (here the arrival of the
+    source rows, after a delay) comes before the remote lane's reads; without
+    that stream the caller's own stream orders it."""
+    say("two-lane remote stream", asked)
+    rows, n, N, d, P = 4, 200, 512, 64, 16
+    g = torch.Generator(device="cuda").manual_seed(2)
+    late = [torch.randn((1, rows, N, d), generator=g, device="cuda") for _ in range(2)]
+    src = [torch.zeros_like(x) for x in late]
+    store = [torch.randn((1, rows, N, d), generator=g, device="cuda") for _ in range(2)]
+    index = torch.rand((rows, N), generator=g, device="cuda").argsort(dim=1)[:, :n].to(torch.int32).contiguous()
+    mask = torch.randint(1, 3, (rows, N), generator=g, device="cuda", dtype=torch.int8)
+    base = torch.arange(rows, dtype=torch.int64, device="cuda") * N
+    per = -(-n // P)
+    pt = (torch.randperm(rows * per, generator=g, device="cuda") * P).to(torch.int32).view(rows, per)
+    pool = [torch.zeros((rows * per * P, d), device="cuda") for _ in range(2)]
+    row_off, mlen = cu(np.arange(rows + 1) * n), cu(np.full(rows, N))
+    buf = StepBuffers.alloc(rows, rows * n)
+    lanes = TwoLane()
+    stream = lanes.remote_stream if asked else torch.cuda.current_stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(20_000_000)
+        for s, x in zip(src, late):
+            s.copy_(x)
+    lanes.gather(row_off=row_off, kv_index=index.view(-1), mask=mask.view(-1), mask_off=base, mask_len=mlen,
+                 store_k=store[0], store_v=store[1], store_base=base, src_k=src[0], src_v=src[1], src_base=base,
+                 page_table=pt, page_size=P, k_pool=pool[0], v_pool=pool[1], buf=buf, reuse=False)
+    order = buf.order.view(rows, n).long()               # remote entries first, then the local ones
+    far = torch.arange(n, device="cuda")[None] < buf.n_remote[:, None]
+    r = torch.arange(rows, device="cuda")[:, None]
+    for x, s, p in zip(late, store, pool):
+        want = torch.where(far[..., None], x[0][r, order], s[0][r, order])
+        at = (pt.long()[:, :, None] + torch.arange(P, device="cuda")).view(rows, -1)[:, :n]
+        assert torch.equal(p[at], want)
