@@ -151,10 +151,10 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
     if (N < W) return;                         // uniform: the count pass writes zeros
     const T *qunit = q_win + (((int64_t)g.b * L + g.l) * Hq + (int64_t)g.h * (Hq / Hkv)) * W * D;
     const T *kunit = k + ((int64_t)g.l * k_layer_rows + (int64_t)g.h * T_ + g.s0) * D;
-    // sampled key i of ns: spread over the keys every row sees
-    // (one in eight, at least 512: a short prompt beside long ones leaves
-    // wavefronts without keys, which only keep the barriers)
-    const int seen = N - W + 1, ns = min(seen, max(512, min(NS, seen / 8 / SPW * SPW))), stride = seen / ns;
+    // ns keys of those every row sees (one in eight, at least 512: a short
+    // prompt beside long ones leaves wavefronts without keys, which only keep
+    // the barriers)
+    const int seen = N - W + 1, ns = min(seen, max(512, min(NS, seen / 8 / SPW * SPW)));
     const bool busy = wave * SPW < ns;         // uniform across the wavefront
     TA<T, D> qf[NRB][M::KS];
 #pragma unroll
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
             const int i = wave * SPW + kb * M::BM + lane % M::BM;
-            const T *p = kunit + (int64_t)(min(i, ns - 1) * (int64_t)stride + stride / 2) * D;
+            const T *p = kunit + (int64_t)sample_key(min(i, ns - 1), ns, seen) * D;
             TA<T, D> kf[M::KS];
 #pragma unroll
             for (int ks = 0; ks < M::KS; ++ks) kf[ks] = M::load_global(p, ks, lane);

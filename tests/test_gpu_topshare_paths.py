@@ -43,6 +43,43 @@ def test_topshare_paths_exact(gpu_lib, dtype, G, W, d, lens, bp, kind):
     np.testing.assert_array_equal(got, ref.astype(np.float32))
 
 
+def _workspace(gpu_lib, q, lens, Hkv):
+    B, L, Hq, W, d = q.shape
+    return torch.full((gpu_lib.score_topshare_workspace_size(B, L, Hq, Hkv, d, W, max(lens)),), 0xA5,
+                      dtype=torch.uint8, device="cuda")
+
+
+def _radix_groups(ws, q, lens, Hkv):
+    """Groups of 32 rows of each unit that took the radix select: the bits of the
+    workspace's words after 98 words per row, one word per unit."""
+    B, L, Hq, W, _ = q.shape
+    units = B * L * Hkv
+    at = units * (Hq // Hkv) * W * 98
+    return [bin(x & 0xffffffff).count("1") for x in ws.view(torch.int32)[at:at + units].tolist()]
+
+
+@pytest.mark.parametrize("n,kind", [(900, "rising"), (1500, "rising"), (2040, "rising"), (8192, "rising"),
+                                    (8192, "period 16"), (8192, "period 64"), (16384, "period 16")])
+def test_topshare_sample_is_fair(gpu_lib, n, kind):
+    """Logits that rise with the position, or whose level repeats: the sampled
+    interval holds every row's threshold, so no row needs the radix select."""
+    say("topshare sample", n, kind)
+    G, W, d, Hkv = 4, 64, 64, 2
+    q = _ints((1, 1, Hkv * G, W, d), 10, 50, n, "bf16")
+    k = _ints((1, Hkv, n, d), -40, 40, n + 1, "bf16")
+    if kind == "rising":
+        level = np.arange(n) * 60 // n
+    else:
+        p = int(kind.split()[1])
+        level = np.random.default_rng(p).integers(-60, 61, p)[np.arange(n) % p]
+    k += torch.from_numpy(level.astype(np.float32)).to(torch.bfloat16)[None, None, :, None]     # whole, below 2^8
+    ws = _workspace(gpu_lib, q, (n,), Hkv)
+    got, cus = _topshare(gpu_lib, q, k, (n,), Hkv, 2000, ws=ws)
+    ref = oracle.score_topshare(q.float().numpy(), k.float().numpy(), cus, Hkv, 2000)
+    np.testing.assert_array_equal(got, ref.astype(np.float32))
+    assert _radix_groups(ws, q, (n,), Hkv) == [0] * Hkv
+
+
 def test_topshare_many_units(gpu_lib):
     """8,388,672 units of one row and two keys: more threads than one launch of
     some passes may hold.  Integer logits, so the larger one (both, if they tie)

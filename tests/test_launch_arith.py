@@ -1,5 +1,6 @@
-"""Host check of the launch arithmetic (csrc/arith.h), compiled by itself: a grid
-dimension holds fewer than 2^32 threads, and the workgroups cover their work."""
+"""Host check of the launch and sampling arithmetic (csrc/arith.h), compiled by
+itself: a grid dimension holds fewer than 2^32 threads, the workgroups cover
+their work, and the sampled keys are spread over all keys and phases."""
 import ctypes
 import os
 import subprocess
@@ -19,7 +20,8 @@ def arith(tmp_path_factory):
                 'extern "C" int slices(int64_t n, int64_t t, int64_t *out) {\n'
                 '    int c = 0;\n'
                 '    sg::launch_slices(n, t, [&](int64_t f, int64_t m) { out[2 * c] = f; out[2 * c + 1] = m; ++c; });\n'
-                '    return c;\n}\n')
+                '    return c;\n}\n'
+                'extern "C" int key(int i, int ns, int seen) { return sg::sample_key(i, ns, seen); }\n')
     subprocess.run(["g++", "-O1", "-Wall", "-Werror", "-std=c++17", "-shared", "-fPIC", "-I",
                     os.path.join(ROOT, "paper_2607_28150_amd", "csrc"), src, "-o", lib], check=True)
     so = ctypes.CDLL(lib)
@@ -49,3 +51,29 @@ def test_launch_slices_cover_their_work(arith, threads):
             assert out[2 * i] == at and 0 < out[2 * i + 1] and out[2 * i + 1] * threads < 2**32
             at += out[2 * i + 1]
         assert at == count
+
+
+@pytest.mark.parametrize("ns", [512, 640, 1024, 2048])
+@pytest.mark.parametrize("ratio", [1, 1.002, 1.5, 1.998, 3.99, 16, 37.3, 4000, 2**18])
+def test_sample_keys_are_spread(arith, ns, ratio):
+    seen = int(ns * ratio)
+    keys = [arith.key(i, ns, seen) for i in range(ns)]
+    assert keys == sorted(keys) and keys[0] >= 0 and keys[-1] < seen
+    if seen == ns:
+        assert keys == list(range(ns))
+    # one key in each of ns equal stretches (a rounding of the stretch's ends
+    # aside), so every stretch of the prompt has its share, the last keys too
+    slack = 1 + seen * 2.0**-22
+    assert all(i * seen / ns - slack <= x <= (i + 1) * seen / ns + slack for i, x in enumerate(keys))
+
+
+@pytest.mark.parametrize("ns,seen", [(512, 8129), (512, 8192), (1024, 16384), (2048, 32705)])
+@pytest.mark.parametrize("period", [2, 3, 8, 16, 32, 64])
+def test_sample_keys_take_every_phase(arith, ns, seen, period):
+    """Keys whose logits repeat are sampled at every phase alike: each phase's
+    count within five standard deviations of its share."""
+    n = [0] * period
+    for i in range(ns):
+        n[arith.key(i, ns, seen) % period] += 1
+    share = ns / period
+    assert max(abs(x - share) for x in n) <= 5 * share**0.5, n
