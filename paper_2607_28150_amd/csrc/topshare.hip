@@ -221,14 +221,20 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
         b = fmaxf(b, smax[w][col]);
     }
     const float top = b;
-    const int64_t nrow = seen + (grp * ROWS + col) % W;
-    const float p = (float)ts_rank(nrow, ratio_bp) / (float)nrow, r = p * ns;
+    // The row's newest keys, which not every row sees, are not sampled: its
+    // rank among the others lies between `r_least` (all of those above it) and
+    // `r_most` (none).  (200 keys, 63 of them the newest rows' own, of rising
+    // logits: with the rank's share alone every unit took hist again, 8 layers
+    // 135 us; 88 now.)
+    const int64_t nrow = seen + (grp * ROWS + col) % W, kk = ts_rank(nrow, ratio_bp);
+    const float per = (float)ns / (float)seen, p = (float)kk / (float)nrow;
+    const float r_most = (float)min(kk, (int64_t)seen) * per, r_least = (float)max(kk - (nrow - seen), (int64_t)0) * per;
     // five standard deviations less a little; near the ends the wanted key lies inside the
-    // sample's extremes unless all `r` expected samples beyond it are missing
-    // (e^-11 from r = 11 on), else the interval is open there (r_hi < 0, r_lo > ns)
-    const float spread = 4.75f * sqrtf(r * (1.f - p)) + 1.f;
-    const int r_hi = max((int)floorf(r - spread), r >= 11.f ? 0 : -1);
-    const int r_lo = min((int)ceilf(r + spread), (float)ns - r >= 11.f ? ns : ns + 1);
+    // sample's extremes unless all the expected samples beyond it are missing
+    // (e^-11 from eleven on), else the interval is open there (r_hi < 0, r_lo > ns)
+    const float spread = 4.75f * sqrtf(p * ns * (1.f - p)) + 1.f;
+    const int r_hi = max((int)floorf(r_least - spread), r_least >= 11.f ? 0 : -1);
+    const int r_lo = min((int)ceilf(r_most + spread), (float)ns - r_most >= 11.f ? ns : ns + 1);
     for (int round = 0; round < 4; ++round) {
         const float sc = b > a ? (float)SB / (b - a) : 0.f;
         if (tid < ROWS) {

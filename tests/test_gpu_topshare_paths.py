@@ -58,6 +58,14 @@ def _radix_groups(ws, q, lens, Hkv):
     return [bin(x & 0xffffffff).count("1") for x in ws.view(torch.int32)[at:at + units].tolist()]
 
 
+def _again_units(ws, q, lens, Hkv):
+    """Units that took the histogram again: the workspace's words after those."""
+    B, L, Hq, W, _ = q.shape
+    units = B * L * Hkv
+    at = units * (Hq // Hkv) * W * 98 + units
+    return sum(x != 0 for x in ws.view(torch.int32)[at:at + units].tolist())
+
+
 @pytest.mark.parametrize("n,kind", [(900, "rising"), (1500, "rising"), (2040, "rising"), (8192, "rising"),
                                     (8192, "period 16"), (8192, "period 64"), (16384, "period 16")])
 def test_topshare_sample_is_fair(gpu_lib, n, kind):
@@ -78,6 +86,23 @@ def test_topshare_sample_is_fair(gpu_lib, n, kind):
     ref = oracle.score_topshare(q.float().numpy(), k.float().numpy(), cus, Hkv, 2000)
     np.testing.assert_array_equal(got, ref.astype(np.float32))
     assert _radix_groups(ws, q, (n,), Hkv) == [0] * Hkv
+
+
+@pytest.mark.parametrize("W,n", [(64, 130), (64, 200), (64, 300), (64, 513), (33, 90)])
+def test_topshare_window_keys_on_top(gpu_lib, W, n):
+    """Short prompts of rising logits: the window's own keys, which the sample
+    leaves out, are the largest, and the first histogram still holds every
+    row's threshold."""
+    say("topshare window keys on top", W, n)
+    G, d, Hkv = 4, 64, 2
+    q = _ints((1, 1, Hkv * G, W, d), 10, 50, n, "bf16")
+    k = _ints((1, Hkv, n, d), -40, 40, n + 1, "bf16")
+    k += torch.from_numpy((np.arange(n) * 200 // n).astype(np.float32)).to(torch.bfloat16)[None, None, :, None]
+    ws = _workspace(gpu_lib, q, (n,), Hkv)
+    got, cus = _topshare(gpu_lib, q, k, (n,), Hkv, 2000, ws=ws)
+    ref = oracle.score_topshare(q.float().numpy(), k.float().numpy(), cus, Hkv, 2000)
+    np.testing.assert_array_equal(got, ref.astype(np.float32))
+    assert _again_units(ws, q, (n,), Hkv) == 0 and _radix_groups(ws, q, (n,), Hkv) == [0] * Hkv
 
 
 def test_topshare_many_units(gpu_lib):
