@@ -53,7 +53,7 @@ namespace sg {
 
 constexpr int TS_BINS = 64;        // bins of a row's interval
 constexpr int TS_CMAX = 92;        // keys a row may gather
-constexpr int TS_LIST = 32;        // of them from one chunk
+constexpr int TS_LIST = 32;        // of them in LDS, per chunk
 constexpr int TS_ROW_WORDS = 99;   // workspace words per row: six below, the rest bins, then lists
 constexpr int TS_UNIT_WORDS = 9;
 static_assert(6 + TS_CMAX <= TS_ROW_WORDS && TS_BINS <= TS_CMAX, "the row lists take the bins' place");
@@ -543,7 +543,20 @@ struct GatherStep {
     uint32_t (&cnt)[NRB];           // values gathered so far
     const float (&xa)[NRB], (&xb)[NRB];
     const int (&pos)[NRB];
-    int lane, key0;
+    int lane, wave, key0, R;
+    uint32_t *gcount, *glist;       // the unit's counts and lists in the workspace
+    // a lane's values go after those the row already has (their order does not
+    // matter: the pick below ranks them)
+    __device__ __forceinline__ void flush(int rb) const {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));    // addresses made here, not held in registers across the caller's loop
+        const uint32_t row = wave * 64 + rb * M::BM + ln % M::BM, n = min(cnt[rb], (uint32_t)CAP);
+        cnt[rb] = 0u;
+        if (row >= (uint32_t)R || n == 0u) return;
+        const uint32_t base = __hip_atomic_fetch_add(gcount + row, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (uint32_t j = 0; j < n && base + j < (uint32_t)TS_CMAX; ++j)
+            glist[row * TS_CMAX + base + j] = mylist[(rb * CAP + j) * 64];
+    }
     __device__ __forceinline__ void operator()(TC<T, D> &acc, int kb, int rb) const {
         uint32_t hits = 0u;
         float last = 0.f;
@@ -619,9 +632,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         barrier_after_loads();      // tile t landed; tile t - 1 done everywhere
         const int key0 = key_begin + t * KT::TK;
         if (t + 1 < ntile) KT::template load<NW>(nxt, kunit, key0 + KT::TK, N, wave, lane);
-        const GatherStep<T, D, NW, MASK> f{mylist, cnt, xa, xb, pos, lane, key0};
+        const GatherStep<T, D, NW, MASK> f{mylist, cnt, xa, xb, pos, lane, wave, key0, R, ws.gcount + u * R,
+                                               ws.list + u * R * TS_CMAX};
         if (MASK) tile_sweep_plain<T, D, true, TKEYS>(cur, q, zero, lane, f);
         else tile_sweep<T, D, true, TKEYS>(cur, q, zero, lane, f);
+        // a list that fills up (logits that follow the position: most of a
+        // row's bin in one chunk) moves to the workspace before the next tile
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+            if (__any(cnt[rb] > (uint32_t)CAP / 2)) f.flush(rb);
     };
     const int nfull = full_tiles(key_begin, ntile, KT::TK, N, W);
     int t = 0;
@@ -633,27 +652,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (t & 1) step(t, kbB, kbA, std::true_type{});
         else step(t, kbA, kbB, std::true_type{});
     }
-    barrier_after_loads();      // every list final, no load in flight
-    // a lane's values go after those the row already has (their order does not
-    // matter: the pick below ranks them)
+    barrier_after_loads();      // no load in flight
+    const GatherStep<T, D, NW, false> f{mylist, cnt, xa, xb, pos, lane, wave, 0, R, ws.gcount + u * R,
+                                        ws.list + u * R * TS_CMAX};
 #pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) {
-        const int row = wave * 64 + rb * M::BM + lane % M::BM;
-        const uint32_t n = min(cnt[rb], (uint32_t)CAP);
-        if (row >= R || n == 0u) continue;
-        const int64_t i = u * R + row;
-        const uint32_t base = __hip_atomic_fetch_add(ws.gcount + i, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (uint32_t j = 0; j < n && base + j < (uint32_t)TS_CMAX; ++j)
-            ws.list[i * TS_CMAX + base + j] = mylist[(rb * CAP + j) * 64];
-    }
+    for (int rb = 0; rb < NRB; ++rb) f.flush(rb);
 }
 
 // The exact value of rank `need` (from the top) among a row's gathered ones: a
 // wavefront takes PICK_ROWS rows, all their loads issued first, a value (or
 // two) per lane, and finds every row's key bit by bit below the bits that the
 // bin's two ends share: the largest key that at least `rank` values reach.  A
-// list cut short (more matches in one chunk than a lane's list holds) sends
-// the row to the radix select.
+// list that does not hold what the histogram counted in its bin (it never is
+// so for numbers) sends the row to the radix select.
 constexpr int PICK_ROWS = 8;
 __global__ __launch_bounds__(256) void ts_pick_kernel(int64_t nrows, int R, int64_t group0, TsWork ws) {
     const int lane = threadIdx.x % 64;
@@ -1001,9 +1012,18 @@ static void launch_topshare(hipStream_t s, const ScorePlan &p, int B, int L, int
         ts_sample_kernel<T, D, NWV, ROWS><<<(unsigned)(n * ceil_div(R, ROWS)), 64 * NWV, 0, s>>>(        \
             B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows, ratio_bp, u0, ws);                  \
     })
-    if (max_seqlen <= 12288) SG_SAMPLE(4, 64);             // 512 keys
-    else if (max_seqlen <= 24576) SG_SAMPLE(8, 64);        // 1024
-    else SG_SAMPLE(8, 32);                                 // 2048
+    // fp32 at d = 128: 64 rows' queries beside as many values spill; 32 rows at a
+    // time read the sample twice, which pays up to 256 rows (4 layers of 4K keys,
+    // 64 / 256 / 512 rows: 301, 577, 1,161 against 315, 588, 1,141 us)
+    bool half = false;
+    if constexpr (sizeof(T) * D > 256) {
+        half = R <= 256;
+        if (half && max_seqlen <= 12288) SG_SAMPLE(2, 32);
+        else if (half && max_seqlen <= 24576) SG_SAMPLE(4, 32);
+    }
+    if (max_seqlen > 24576) SG_SAMPLE(8, 32);              // 2048 keys
+    else if (!half && max_seqlen > 12288) SG_SAMPLE(8, 64);    // 1024
+    else if (!half) SG_SAMPLE(4, 64);                      // 512
 #undef SG_SAMPLE
     const dim3 dgrid((unsigned)units, (unsigned)ceil_div(R, TS_DIGIT_THREADS));
     ts_hist_kernel<T, D, NW, false><<<grid, 64 * NW, 0, s>>>(B, L, Hq, Hkv, W, cu_seqlens, ntok, q, kk, k_layer_rows,

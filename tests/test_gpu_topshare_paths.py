@@ -105,6 +105,25 @@ def test_topshare_window_keys_on_top(gpu_lib, W, n):
     assert _again_units(ws, q, (n,), Hkv) == 0 and _radix_groups(ws, q, (n,), Hkv) == [0] * Hkv
 
 
+@pytest.mark.parametrize("dtype,G,d,n,B", [("bf16", 4, 64, 2048, 64), ("f32", 2, 64, 2048, 64), ("bf16", 8, 128, 4096, 16)])
+def test_topshare_bins_in_one_chunk(gpu_lib, dtype, G, d, n, B):
+    """Logits that follow the position: all the keys of a row's bin lie in a few
+    neighbouring tiles of one 2,048-key chunk, and are gathered all the same
+    (half of the key's step in noise, so that no two logits tie)."""
+    say("topshare bins in one chunk", dtype, G, d, n, B)
+    W, Hkv, L = 16, 8, 2
+    q = _ints((B, L, Hkv * G, W, d), 30, 50, n, dtype)
+    k = _ints((L, Hkv, B * n, d), -1, 1, n + 1, dtype)
+    k += torch.from_numpy(np.tile(np.arange(n) * 250 // n, B).astype(np.float32)).to(k.dtype)[None, None, :, None]
+    ws = _workspace(gpu_lib, q, [n] * B, Hkv)
+    got, cus = _topshare(gpu_lib, q, k, [n] * B, Hkv, 2000, ws=ws)
+    assert sum(_radix_groups(ws, q, [n] * B, Hkv)) == 0
+    for b in (0, B - 1):
+        ref = oracle.score_topshare(q[b:b + 1].float().numpy(), k[:, :, b * n:(b + 1) * n].float().numpy(), [0, n], Hkv,
+                                    2000)
+        np.testing.assert_array_equal(got[:, :, b * n:(b + 1) * n], ref.astype(np.float32))
+
+
 def test_topshare_many_units(gpu_lib):
     """8,388,672 units of one row and two keys: more threads than one launch of
     some passes may hold.  Integer logits, so the larger one (both, if they tie)
