@@ -220,7 +220,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
         a = fminf(a, smin[w][col]);
         b = fmaxf(b, smax[w][col]);
     }
-    const float top = b;
+    const float top = b, quarter_range = 0.25f * (b - a);
     // The row's newest keys, which not every row sees, are not sampled: its
     // rank among the others lies between `r_least` (all of those above it) and
     // `r_most` (none).  (200 keys, 63 of them the newest rows' own, of rising
@@ -305,10 +305,15 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
         if (__syncthreads_or(wide) == 0 && round >= (NS > 512 ? 1 : 0)) break;     // uniform
     }
     if (owner) {
-        // open ends: room beyond the sample's extremes
-        if (r_hi < 0) b = top + 4.f * (top - a);
+        // open ends: room beyond the sample's extremes, where a few tens of
+        // keys lie; those past the room are gathered as if it were a bin
+        // (digit).  With an interval meant to cover them all, ranks at the
+        // ends took hist again and the radix select (4 layers of 16K keys, the
+        // largest or all but the smallest of each row: 832 and 1,135 us, now
+        // 209 and 211)
+        if (r_hi < 0) b = top + fmaxf(top - a, quarter_range);
         else if (b >= top) b = top + 1e-3f * (top - a);
-        if (r_lo > ns) a -= b - a;
+        if (r_lo > ns) a -= fmaxf(b - a, quarter_range);
         if (!(b > a)) {                        // a constant sample
             const float e = fmaxf(fabsf(a) * 1e-5f, 1e-20f);
             a -= e;
@@ -489,20 +494,34 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
                 above += c[j];
             }
         }
-        if (bin >= 0) {
+        const int64_t below = n - above;       // keys below the interval
+        bool found = bin >= 0;
+        if (found) {
             xa = key_value(ts_bound(TS_LOW + 1 + bin, scale, off));
             xb = key_value(ts_bound(TS_LOW + 2 + bin, scale, off) - 1u);
+        } else if (scale > 0.f && !inside && above_in <= TS_CMAX) {
+            // few keys above the interval, the wanted one among them
+            xa = key_value(ts_bound(TS_LOW + 1 + TS_BINS, scale, off));
+            rest = kk;
+            in_bin = (uint32_t)above_in;
+            found = true;
+        } else if (scale > 0.f && inside && below <= TS_CMAX) {
+            xa = -INFINITY;
+            xb = key_value(ts_bound(TS_LOW + 1, scale, off) - 1u);
+            rest = kk - above;
+            in_bin = (uint32_t)below;
+            found = true;
         }
-        if (bin >= 0 && in_bin <= (uint32_t)TS_CMAX) {
+        if (found && in_bin <= (uint32_t)TS_CMAX) {
             need = (uint32_t)rest | in_bin << 16;
         } else {
             // another interval: the bin, or (the sample misjudged the row) the
-            // stretch above or below the last one
+            // stretch above or below the last one, far where few keys lie
             const float a = (1.f - off) / scale, w = 1.f / scale;
-            // keys above: few of them may lie far out
             const float up = above_in <= 4 * TS_CMAX ? 16.f * w : w;
-            const float na = bin >= 0 ? xa : inside ? a - w : a + w;
-            const float nb = bin >= 0 ? xb + (xb - xa) * 1e-3f : inside ? a : a + w + up;
+            const float down = below <= 4 * TS_CMAX ? 16.f * w : w;
+            const float na = found ? xa : inside ? a - down : a + w;
+            const float nb = found ? xb + (xb - xa) * 1e-3f : inside ? a : a + w + up;
             const float ns = 1.f / (nb - na), no = 1.f - na * ns;
             if (!AGAIN && nb > na && ns > 0.f && ns < INFINITY && fabsf(no) < INFINITY) {
                 need = TS_AGAIN;
@@ -513,7 +532,7 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
                 ws.again[u] = 1u;                          // every writer stores the same value
             } else {
                 need = TS_RADIX;
-                if (bin < 0) xa = xb = __builtin_nanf("");
+                if (!found) xa = xb = __builtin_nanf("");
                 atomicOr(ws.fail + u, 1u << (r / 32));
             }
         }

@@ -124,6 +124,25 @@ def test_topshare_bins_in_one_chunk(gpu_lib, dtype, G, d, n, B):
         np.testing.assert_array_equal(got[:, :, b * n:(b + 1) * n], ref.astype(np.float32))
 
 
+@pytest.mark.parametrize("bp", [1, 10, 100, 9990, 9999])
+@pytest.mark.parametrize("dtype,n,kind", [("bf16", 12000, "plain"), ("bf16", 16384, "plain"), ("bf16", 9000, "outliers"),
+                                          ("f32", 5000, "plain"), ("bf16", 700, "plain")])
+def test_topshare_ranks_at_the_ends(gpu_lib, dtype, n, kind, bp):
+    """The largest keys, or all but the smallest: those beyond the sample's
+    extremes are gathered, so no row needs the radix select."""
+    say("topshare ranks at the ends", dtype, n, kind, bp)
+    G, W, d, Hkv = 4, 16, 64, 2
+    q = _ints((1, 1, Hkv * G, W, d), -40, 40, n, dtype)
+    k = _ints((1, Hkv, n, d), -40, 40, n + 1, dtype)
+    if kind == "outliers":                               # still exact: below 2^24
+        k[:, :, 100::1500] *= 32
+    ws = _workspace(gpu_lib, q, (n,), Hkv)
+    got, cus = _topshare(gpu_lib, q, k, (n,), Hkv, bp, ws=ws)
+    ref = oracle.score_topshare(q.float().numpy(), k.float().numpy(), cus, Hkv, bp)
+    np.testing.assert_array_equal(got, ref.astype(np.float32))
+    assert _radix_groups(ws, q, (n,), Hkv) == [0] * Hkv
+
+
 def test_topshare_many_units(gpu_lib):
     """8,388,672 units of one row and two keys: more threads than one launch of
     some passes may hold.  Integer logits, so the larger one (both, if they tie)
