@@ -24,19 +24,23 @@
 //            than TS_CMAX keys take hist and digit once more, over the next
 //            interval or that bin (every other unit returns at once);
 //   gather : the values inside a row's bin (a few tens at most) are appended
-//            to the row's list, in LDS, then in the workspace;
-//   pick   : the exact k-th largest among them is the row's threshold;
-//   radix  : rows still unresolved (ties, NaN) take an exact radix select over
-//            the logits' bit patterns, one workgroup per 32 rows with such a
-//            row (every other one returns at once);
+//            to the row's list, in LDS, then in the workspace; of a bin that
+//            still holds more (ties) the smallest and largest are kept;
+//   pick   : the exact k-th largest among them is the row's threshold, or the
+//            one value of a bin of ties;
+//   radix  : rows still unresolved (different ties side by side, NaN) take an
+//            exact radix select over the logits' bit patterns, one workgroup
+//            per 32 rows with such a row (every other one returns at once);
 //   count  : each key's picks, counted against the rows' thresholds.
 //
 // Against a radix select in 6-bit digits for all rows (three histogram passes,
 // gather and count, one workgroup per CU in each): 32 layers x 8 heads of 8K
-// keys, 256 rows each, at 20%: 1.14 -> 0.62-0.65 ms (sample 62, hist 187, digit
+// keys, 256 rows each, at 20%: 1.14 -> 0.60-0.65 ms (sample 62, hist 187, digit
 // 13, gather 190, pick 25, count 137 us, the three idle launches 14 us); one
-// unit in ten or so has a row that takes hist again.  Rows of nothing but ties
-// (every logit one of a few values) are slower: they reach the radix select.
+// unit in ten or so has a row that takes hist again.  Rows of ties take hist
+// again and the plain loop of gather.  8 layers of 8K keys, every logit zero /
+// one of a few values / repeating every 64 keys: 0.32 / 0.33 / 0.48 ms; with the
+// radix select in gather's place 1.13 / 1.00 / 0.81, with one for all rows 0.63.
 //
 // A logit's bits are the same in every pass: the same MFMA operands in the
 // same contraction order (C = K Q^T in hist and gather, Q K^T in count).  The
@@ -61,17 +65,23 @@ static_assert(6 + TS_CMAX <= TS_ROW_WORDS && TS_BINS <= TS_CMAX, "the row lists 
 // The call's workspace.
 struct TsWork {
     float *xa, *xb;        // [rows] interval scale and offset, then the bounds of the row's bin
-    uint32_t *need;        // [rows] rank inside the bin | keys in the bin << 16; 0: settled; TS_AGAIN; TS_RADIX
+    uint32_t *need;        // [rows] rank inside the bin | keys in the bin << 16; 0: settled; TS_AGAIN; TS_TIED; TS_RADIX
     uint32_t *above;       // [rows] keys above the interval
     uint32_t *gcount;      // [rows] keys gathered
     float *thr;            // [rows] threshold
     uint32_t *hist;        // [units][TS_BINS][R] bins
     uint32_t *list;        // [rows][TS_CMAX] gathered values (in the bins' place)
     uint32_t *fail;        // [units] bit per 32 rows: a row needs the radix select
-    uint32_t *again;       // [units] a row of the unit needs another histogram
+    uint32_t *again;       // [units] a row of the unit needs another histogram; TS_TIED_UNIT: one was left tied
 };
+constexpr uint32_t TS_TIED_UNIT = 2u;
 constexpr uint32_t TS_AGAIN = 0xffffffffu;      // need: another histogram over the interval in xa, xb
 constexpr uint32_t TS_RADIX = 0xfffffffeu;      // need: the radix select, between xa and xb (NaN: anywhere)
+// need: more keys in the bin than a row may gather, in a bin that is narrow by
+// now, so most likely equal: gather takes their smallest and largest order key
+// (in the words of thr and gcount) instead of a list
+constexpr uint32_t TS_TIED = 0xfffffffdu;
+constexpr uint32_t TS_TIED_LANE = 0x80000000u;  // gather's count of a lane of such a row
 
 __device__ __forceinline__ uint32_t order_key(float f) {
     const uint32_t x = __float_as_uint(f);
@@ -520,7 +530,7 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
             const float a = (1.f - off) / scale, w = 1.f / scale;
             const float up = above_in <= 4 * TS_CMAX ? 16.f * w : w;
             const float down = below <= 4 * TS_CMAX ? 16.f * w : w;
-            const float na = found ? xa : inside ? a - down : a + w;
+            const float na = found ? xa - (xb - xa) * 1e-3f : inside ? a - down : a + w;
             const float nb = found ? xb + (xb - xa) * 1e-3f : inside ? a : a + w + up;
             const float ns = 1.f / (nb - na), no = 1.f - na * ns;
             if (!AGAIN && nb > na && ns > 0.f && ns < INFINITY && fabsf(no) < INFINITY) {
@@ -529,10 +539,15 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
                 xb = no;
                 ws.above[i] = 0u;
                 for (int d = 0; d < TS_BINS; ++d) h[(int64_t)d * R] = 0u;
-                ws.again[u] = 1u;                          // every writer stores the same value
+                atomicMax(ws.again + u, 1u);
+            } else if (found) {
+                need = TS_TIED;
+                atomicMax(ws.again + u, TS_TIED_UNIT);
+                thr = __uint_as_float(0xffffffffu);
+                ws.gcount[i] = 0u;
             } else {
                 need = TS_RADIX;
-                if (!found) xa = xb = __builtin_nanf("");
+                xa = xb = __builtin_nanf("");
                 atomicOr(ws.fail + u, 1u << (r / 32));
             }
         }
@@ -554,7 +569,9 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
 // them one by one.  (Masks per value, joined and tested in scalar registers,
 // took 254 us for the pass at 8K keys; a list entry turns up in nearly every
 // block.)
-template <typename T, int D, int NW, bool MASK>
+// TIED: the unit has rows that want only the smallest and largest value of
+// their bin, kept in the first two words of the lane's list.
+template <typename T, int D, int NW, bool MASK, bool TIED = false>
 struct GatherStep {
     using M = MT<T, D>;
     static constexpr int NRB = QFrags<T, D>::NRB, CAP = TS_LIST * M::BM / 64;   // entries per lane and row block
@@ -563,15 +580,20 @@ struct GatherStep {
     const float (&xa)[NRB], (&xb)[NRB];
     const int (&pos)[NRB];
     int lane, wave, key0, R;
-    uint32_t *gcount, *glist;       // the unit's counts and lists in the workspace
+    uint32_t *gcount, *glist, *gmin;        // the unit's counts, lists and tied rows' smallest keys in the workspace
     // a lane's values go after those the row already has (their order does not
     // matter: the pick below ranks them)
     __device__ __forceinline__ void flush(int rb) const {
         int ln = lane;
         asm volatile("" : "+v"(ln));    // addresses made here, not held in registers across the caller's loop
         const uint32_t row = wave * 64 + rb * M::BM + ln % M::BM, n = min(cnt[rb], (uint32_t)CAP);
-        cnt[rb] = 0u;
         if (row >= (uint32_t)R || n == 0u) return;
+        if (TIED && cnt[rb] >= TS_TIED_LANE) {
+            atomicMin(gmin + row, mylist[rb * CAP * 64]);
+            atomicMax(gcount + row, mylist[(rb * CAP + 1) * 64]);
+            return;
+        }
+        cnt[rb] = 0u;
         const uint32_t base = __hip_atomic_fetch_add(gcount + row, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (uint32_t j = 0; j < n && base + j < (uint32_t)TS_CMAX; ++j)
             glist[row * TS_CMAX + base + j] = mylist[(rb * CAP + j) * 64];
@@ -585,6 +607,21 @@ struct GatherStep {
             if (MASK) h = h && key0 + kb * M::BM + M::crow(v, lane) <= pos[rb];
             last = h ? acc[v] : last;
             hits = hits + hits + (h ? 1u : 0u);
+        }
+        if (TIED && __any(hits != 0u && cnt[rb] >= TS_TIED_LANE)) {
+            float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+            for (int v = 0; v < M::NV; ++v) {
+                const bool h = (hits >> (M::NV - 1 - v)) & 1u;
+                lo = fminf(lo, h ? acc[v] : lo);
+                hi = fmaxf(hi, h ? acc[v] : hi);
+            }
+            if (hits != 0u && cnt[rb] >= TS_TIED_LANE) {
+                uint32_t *l = mylist + rb * CAP * 64;
+                l[0] = min(l[0], order_key(lo));
+                l[64] = max(l[64], order_key(hi));
+                hits = 0u;
+            }
         }
         auto add = [&](float x) {
             if (cnt[rb] < (uint32_t)CAP) mylist[(rb * CAP + cnt[rb]) * 64] = __float_as_uint(x);
@@ -601,7 +638,7 @@ struct GatherStep {
 };
 
 template <typename T, int D, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void ts_gather_kernel(
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(T) * D * 8 / NW <= 128 ? 4 : 2))) void ts_gather_kernel(
     int B, int L, int Hq, int Hkv, int W, const int32_t *__restrict__ cu_seqlens, int64_t T_,
     const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int nchunk, int chunk_keys,
     TsWork ws) {
@@ -633,47 +670,59 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     uint32_t cnt[NRB];
     float xa[NRB], xb[NRB];
     int pos[NRB];
+    uint32_t *mylist = lists + wave * (NRB * CAP * 64) + lane;
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
         const int row = wave * 64 + rb * M::BM + lane % M::BM;
         pos[rb] = row < R ? N - W + row % W : -1;
-        const bool on = row < R && ws.need[u * R + row] != TS_RADIX;
-        xa[rb] = on ? ws.xa[u * R + row] : INFINITY;
-        xb[rb] = on ? ws.xb[u * R + row] : INFINITY;
-        cnt[rb] = 0u;
+        const uint32_t need = row < R ? ws.need[u * R + row] : TS_RADIX;
+        xa[rb] = need != TS_RADIX ? ws.xa[u * R + row] : INFINITY;
+        xb[rb] = need != TS_RADIX ? ws.xb[u * R + row] : INFINITY;
+        cnt[rb] = need == TS_TIED ? TS_TIED_LANE : 0u;
+        if (need == TS_TIED) {
+            mylist[rb * CAP * 64] = 0xffffffffu;
+            mylist[(rb * CAP + 1) * 64] = 0u;
+        }
     }
-    uint32_t *mylist = lists + wave * (NRB * CAP * 64) + lane;
     TC<T, D> zero[NRB];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) zero[rb] = M::zero();
-    auto step = [&](int t, char *cur, char *nxt, auto mask) {
-        constexpr bool MASK = decltype(mask)::value;
+    uint32_t *gcount = ws.gcount + u * R, *glist = ws.list + u * R * TS_CMAX;
+    uint32_t *gmin = reinterpret_cast<uint32_t *>(ws.thr) + u * R;
+    auto step = [&](int t, char *cur, char *nxt, auto mask, auto ties) {
+        constexpr bool MASK = decltype(mask)::value, TIED = decltype(ties)::value;
         barrier_after_loads();      // tile t landed; tile t - 1 done everywhere
         const int key0 = key_begin + t * KT::TK;
         if (t + 1 < ntile) KT::template load<NW>(nxt, kunit, key0 + KT::TK, N, wave, lane);
-        const GatherStep<T, D, NW, MASK> f{mylist, cnt, xa, xb, pos, lane, wave, key0, R, ws.gcount + u * R,
-                                               ws.list + u * R * TS_CMAX};
+        const GatherStep<T, D, NW, MASK, TIED> f{mylist, cnt, xa, xb, pos, lane, wave, key0, R, gcount, glist, gmin};
         if (MASK) tile_sweep_plain<T, D, true, TKEYS>(cur, q, zero, lane, f);
         else tile_sweep<T, D, true, TKEYS>(cur, q, zero, lane, f);
         // a list that fills up (logits that follow the position: most of a
         // row's bin in one chunk) moves to the workspace before the next tile
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb)
-            if (__any(cnt[rb] > (uint32_t)CAP / 2)) f.flush(rb);
+            if (__any(cnt[rb] > (uint32_t)CAP / 2 && cnt[rb] < TS_TIED_LANE)) f.flush(rb);
     };
-    const int nfull = full_tiles(key_begin, ntile, KT::TK, N, W);
-    int t = 0;
-    for (; t + 1 < nfull; t += 2) {
-        step(t, kbA, kbB, std::false_type{});
-        step(t + 1, kbB, kbA, std::false_type{});
-    }
-    for (; t < ntile; ++t) {
-        if (t & 1) step(t, kbB, kbA, std::true_type{});
-        else step(t, kbA, kbB, std::true_type{});
+    // (rare: one plain loop, so that the tied rows' work costs the others nothing)
+    if (ws.again[u] == TS_TIED_UNIT) {         // uniform
+        for (int t = 0; t < ntile; ++t) {
+            if (t & 1) step(t, kbB, kbA, std::true_type{}, std::true_type{});
+            else step(t, kbA, kbB, std::true_type{}, std::true_type{});
+        }
+    } else {
+        const int nfull = full_tiles(key_begin, ntile, KT::TK, N, W);
+        int t = 0;
+        for (; t + 1 < nfull; t += 2) {
+            step(t, kbA, kbB, std::false_type{}, std::false_type{});
+            step(t + 1, kbB, kbA, std::false_type{}, std::false_type{});
+        }
+        for (; t < ntile; ++t) {
+            if (t & 1) step(t, kbB, kbA, std::true_type{}, std::false_type{});
+            else step(t, kbA, kbB, std::true_type{}, std::false_type{});
+        }
     }
     barrier_after_loads();      // no load in flight
-    const GatherStep<T, D, NW, false> f{mylist, cnt, xa, xb, pos, lane, wave, 0, R, ws.gcount + u * R,
-                                        ws.list + u * R * TS_CMAX};
+    const GatherStep<T, D, NW, true, true> f{mylist, cnt, xa, xb, pos, lane, wave, 0, R, gcount, glist, gmin};
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) f.flush(rb);
 }
@@ -703,6 +752,16 @@ __global__ __launch_bounds__(256) void ts_pick_kernel(int64_t nrows, int R, int6
     }
     // lane j: row i0 + j
     if (need == TS_RADIX) need = 0u;
+    if (need == TS_TIED) {             // one value (-0 and +0 are equal) is the threshold
+        const uint32_t lo = reinterpret_cast<const uint32_t *>(ws.thr)[mine];
+        const float x = key_value(lo), y = key_value(got);
+        if (lane < PICK_ROWS) {
+            ws.thr[mine] = y;
+            ws.xa[mine] = x == 0.f ? -0.f : x;         // else: the radix select between them
+            ws.xb[mine] = y == 0.f ? 0.f : y;
+        }
+        if (x == y) need = 0u;
+    }
     if (need != 0u && got != need >> 16) {
         const int64_t u = mine / R;
         if (lane < PICK_ROWS) {

@@ -143,6 +143,31 @@ def test_topshare_ranks_at_the_ends(gpu_lib, dtype, n, kind, bp):
     assert _radix_groups(ws, q, (n,), Hkv) == [0] * Hkv
 
 
+@pytest.mark.parametrize("dtype,G,W,d,n,kind", [
+    ("bf16", 4, 64, 64, 8192, "zeros"), ("bf16", 4, 64, 128, 5000, "few"), ("f32", 4, 16, 64, 3000, "few"),
+    ("bf16", 8, 64, 64, 4096, "few"), ("bf16", 2, 64, 64, 8192, "period 16"), ("bf16", 4, 32, 128, 8191, "period 64"),
+    ("f32", 2, 33, 128, 4000, "period 16"), ("bf16", 1, 40, 64, 30000, "period 64"), ("bf16", 4, 64, 64, 9001, "half")])
+def test_topshare_ties_settle(gpu_lib, dtype, G, W, d, n, kind):
+    """More equal logits at a row's threshold than it may gather (one value, a
+    few, repeated keys): found equal, not handed to the radix select."""
+    say("topshare ties", dtype, G, W, d, n, kind)
+    Hkv = 2
+    q = _ints((1, 1, Hkv * G, W, d), -1 if kind == "few" else -40, 1 if kind == "few" else 40, n, dtype)
+    k = _ints((1, Hkv, n, d), -1 if kind == "few" else -40, 1 if kind == "few" else 40, n + 1, dtype)
+    if kind == "zeros":
+        k *= -0.0
+    elif kind == "half":
+        k[:, :, ::2] = 0
+    elif kind != "few":
+        k = k[:, :, torch.arange(n) % int(kind.split()[1])].contiguous()
+    for bp in (700, 5000):
+        ws = _workspace(gpu_lib, q, (n,), Hkv)
+        got, cus = _topshare(gpu_lib, q, k, (n,), Hkv, bp, ws=ws)
+        ref = oracle.score_topshare(q.float().numpy(), k.float().numpy(), cus, Hkv, bp)
+        np.testing.assert_array_equal(got, ref.astype(np.float32))
+        assert sum(_radix_groups(ws, q, (n,), Hkv)) <= 1, bp      # (of up to 32 groups of rows)
+
+
 def test_topshare_many_units(gpu_lib):
     """8,388,672 units of one row and two keys: more threads than one launch of
     some passes may hold.  Integer logits, so the larger one (both, if they tie)
