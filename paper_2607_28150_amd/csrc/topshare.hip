@@ -505,22 +505,21 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
             }
         }
         const int64_t below = n - above;       // keys below the interval
-        bool found = bin >= 0;
-        if (found) {
-            xa = key_value(ts_bound(TS_LOW + 1 + bin, scale, off));
-            xb = key_value(ts_bound(TS_LOW + 2 + bin, scale, off) - 1u);
-        } else if (scale > 0.f && !inside && above_in <= TS_CMAX) {
-            // few keys above the interval, the wanted one among them
-            xa = key_value(ts_bound(TS_LOW + 1 + TS_BINS, scale, off));
+        if (bin < 0 && scale > 0.f && !inside && above_in <= TS_CMAX) {
+            // few keys above the interval, the wanted one among them: a bin
+            bin = TS_BINS;
             rest = kk;
             in_bin = (uint32_t)above_in;
+        }
+        bool found = bin >= 0;
+        if (!found && scale > 0.f && inside && below <= TS_CMAX) {      // or below it (bin -1)
             found = true;
-        } else if (scale > 0.f && inside && below <= TS_CMAX) {
-            xa = -INFINITY;
-            xb = key_value(ts_bound(TS_LOW + 1, scale, off) - 1u);
             rest = kk - above;
             in_bin = (uint32_t)below;
-            found = true;
+        }
+        if (found) {
+            xa = key_value(ts_bound(TS_LOW + 1 + bin, scale, off));
+            xb = bin < TS_BINS ? key_value(ts_bound(TS_LOW + 2 + bin, scale, off) - 1u) : INFINITY;
         }
         if (found && in_bin <= (uint32_t)TS_CMAX) {
             need = (uint32_t)rest | in_bin << 16;
@@ -569,9 +568,10 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
 // them one by one.  (Masks per value, joined and tested in scalar registers,
 // took 254 us for the pass at 8K keys; a list entry turns up in nearly every
 // block.)
-// TIED: the unit has rows that want only the smallest and largest value of
-// their bin, kept in the first two words of the lane's list.
-template <typename T, int D, int NW, bool MASK, bool TIED = false>
+// CARE: for units with rows that want only the smallest and largest value of
+// their bin (kept in the first two words of the lane's list) and for chunks in
+// which a list ran over: a list that would run over first moves to the workspace.
+template <typename T, int D, int NW, bool MASK, bool CARE = false>
 struct GatherStep {
     using M = MT<T, D>;
     static constexpr int NRB = QFrags<T, D>::NRB, CAP = TS_LIST * M::BM / 64;   // entries per lane and row block
@@ -588,7 +588,7 @@ struct GatherStep {
         asm volatile("" : "+v"(ln));    // addresses made here, not held in registers across the caller's loop
         const uint32_t row = wave * 64 + rb * M::BM + ln % M::BM, n = min(cnt[rb], (uint32_t)CAP);
         if (row >= (uint32_t)R || n == 0u) return;
-        if (TIED && cnt[rb] >= TS_TIED_LANE) {
+        if (cnt[rb] >= TS_TIED_LANE) {
             atomicMin(gmin + row, mylist[rb * CAP * 64]);
             atomicMax(gcount + row, mylist[(rb * CAP + 1) * 64]);
             return;
@@ -608,7 +608,7 @@ struct GatherStep {
             last = h ? acc[v] : last;
             hits = hits + hits + (h ? 1u : 0u);
         }
-        if (TIED && __any(hits != 0u && cnt[rb] >= TS_TIED_LANE)) {
+        if (CARE && __any(hits != 0u && cnt[rb] >= TS_TIED_LANE)) {
             float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
             for (int v = 0; v < M::NV; ++v) {
@@ -623,6 +623,8 @@ struct GatherStep {
                 hits = 0u;
             }
         }
+        static_assert(M::NV <= CAP, "an empty list holds a block's values");
+        if (CARE && __any(cnt[rb] < TS_TIED_LANE && cnt[rb] + (uint32_t)__popc(hits) > (uint32_t)CAP)) flush(rb);
         auto add = [&](float x) {
             if (cnt[rb] < (uint32_t)CAP) mylist[(rb * CAP + cnt[rb]) * 64] = __float_as_uint(x);
             ++cnt[rb];
@@ -653,6 +655,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     int64_t u;
     int chunk;
     unit_chunk((int64_t)L * Hkv * B, nchunk, u, chunk);
+    const bool tied = ws.again[u] == TS_TIED_UNIT;     // uniform
     const UnitGeom g = unit_geom(u, B, Hkv, cu_seqlens, T_);
     const int G = Hq / Hkv, R = G * W;
     const int N = (int)g.N;
@@ -689,27 +692,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     for (int rb = 0; rb < NRB; ++rb) zero[rb] = M::zero();
     uint32_t *gcount = ws.gcount + u * R, *glist = ws.list + u * R * TS_CMAX;
     uint32_t *gmin = reinterpret_cast<uint32_t *>(ws.thr) + u * R;
-    auto step = [&](int t, char *cur, char *nxt, auto mask, auto ties) {
-        constexpr bool MASK = decltype(mask)::value, TIED = decltype(ties)::value;
+    auto step = [&](int t, char *cur, char *nxt, auto mask, auto care) {
+        constexpr bool MASK = decltype(mask)::value, CARE = decltype(care)::value;
         barrier_after_loads();      // tile t landed; tile t - 1 done everywhere
         const int key0 = key_begin + t * KT::TK;
         if (t + 1 < ntile) KT::template load<NW>(nxt, kunit, key0 + KT::TK, N, wave, lane);
-        const GatherStep<T, D, NW, MASK, TIED> f{mylist, cnt, xa, xb, pos, lane, wave, key0, R, gcount, glist, gmin};
+        const GatherStep<T, D, NW, MASK, CARE> f{mylist, cnt, xa, xb, pos, lane, wave, key0, R, gcount, glist, gmin};
         if (MASK) tile_sweep_plain<T, D, true, TKEYS>(cur, q, zero, lane, f);
         else tile_sweep<T, D, true, TKEYS>(cur, q, zero, lane, f);
-        // a list that fills up (logits that follow the position: most of a
-        // row's bin in one chunk) moves to the workspace before the next tile
-#pragma unroll
-        for (int rb = 0; rb < NRB; ++rb)
-            if (__any(cnt[rb] > (uint32_t)CAP / 2 && cnt[rb] < TS_TIED_LANE)) f.flush(rb);
     };
-    // (rare: one plain loop, so that the tied rows' work costs the others nothing)
-    if (ws.again[u] == TS_TIED_UNIT) {         // uniform
-        for (int t = 0; t < ntile; ++t) {
-            if (t & 1) step(t, kbB, kbA, std::true_type{}, std::true_type{});
-            else step(t, kbA, kbB, std::true_type{}, std::true_type{});
-        }
-    } else {
+    bool care = tied;
+    if (!care) {
         const int nfull = full_tiles(key_begin, ntile, KT::TK, N, W);
         int t = 0;
         for (; t + 1 < nfull; t += 2) {
@@ -720,11 +713,40 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
             if (t & 1) step(t, kbB, kbA, std::true_type{}, std::false_type{});
             else step(t, kbA, kbB, std::true_type{}, std::false_type{});
         }
-    }
-    barrier_after_loads();      // no load in flight
-    const GatherStep<T, D, NW, true, true> f{mylist, cnt, xa, xb, pos, lane, wave, 0, R, gcount, glist, gmin};
+        barrier_after_loads();      // the tiles are done with, no load in flight
+        // a list that ran over anywhere in the workgroup (logits that follow the
+        // position put most of a row's bin into one chunk): the chunk again, with
+        // care.  32 layers of 8K keys, rising logits: 0.94 ms; 1.36 with the radix
+        // select for such rows; 0.68 with full lists moved between tiles, which
+        // took every call 8 to 10 of the pass's 190 us.
+        bool over = false;
 #pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) f.flush(rb);
+        for (int rb = 0; rb < NRB; ++rb) over |= cnt[rb] > (uint32_t)CAP;
+        int *flags = reinterpret_cast<int *>(kbA);
+        if (lane == 0) flags[wave] = 0;
+        if (over) flags[wave] = 1;
+        __syncthreads();
+        int any = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) any |= flags[w];
+        care = __builtin_amdgcn_readfirstlane(any) != 0;
+        if (care) {                 // uniform across the workgroup
+            __syncthreads();        // every flag read
+            KT::template load<NW>(kbA, kunit, key_begin, N, wave, lane);
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) cnt[rb] = 0u;
+        }
+    }
+    if (care) {
+        for (int t = 0; t < ntile; ++t) {
+            if (t & 1) step(t, kbB, kbA, std::true_type{}, std::true_type{});
+            else step(t, kbA, kbB, std::true_type{}, std::true_type{});
+        }
+        barrier_after_loads();      // no load in flight
+    }
+    const GatherStep<T, D, NW, true, true> rest{mylist, cnt, xa, xb, pos, lane, wave, 0, R, gcount, glist, gmin};
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) rest.flush(rb);
 }
 
 // The exact value of rank `need` (from the top) among a row's gathered ones: a
