@@ -168,6 +168,44 @@ def test_topshare_ties_settle(gpu_lib, dtype, G, W, d, n, kind):
         assert sum(_radix_groups(ws, q, (n,), Hkv)) <= 1, bp      # (of up to 32 groups of rows)
 
 
+@pytest.mark.parametrize("dtype,G,W,d,n,bp", [("bf16", 4, 16, 64, 3000, 2000), ("f32", 2, 33, 64, 1500, 300),
+                                              ("bf16", 8, 64, 128, 5000, 9000), ("bf16", 1, 16, 64, 500, 100)])
+@pytest.mark.parametrize("kind", ["inf", "nan", "many nan", "all"])
+def test_topshare_not_finite(gpu_lib, dtype, G, W, d, n, bp, kind):
+    """Infinite and NaN logits, in the documented order of their bit patterns: a
+    NaN takes a rank, above +inf or with its sign bit set below -inf, and is
+    never picked itself.  (The matrix instructions of fp32 keep the key's NaN,
+    those of bf16 make one with the sign bit.)"""
+    low = dtype == "bf16"
+    say("topshare not finite", dtype, G, W, d, n, bp, kind)
+    Hkv = 2
+    q = _ints((1, 1, Hkv * G, W, d), -20, 20, n, dtype)
+    q[..., 0] = torch.where(q[..., 0] >= 0, 3.0, -3.0).to(q.dtype)      # an infinite key channel: +-inf, no NaN
+    k = _ints((1, Hkv, n, d), -40, 40, n + 1, dtype)
+    g = np.random.default_rng(n)
+    if kind in ("inf", "all"):
+        k[0, :, g.choice(n, max(1, n // 40), replace=False), 0] = float("inf")
+        k[0, :, g.choice(n, max(1, n // 40), replace=False), 0] = float("-inf")
+    if kind in ("nan", "many nan", "all"):
+        k[0, :, g.choice(n, n // 3 if kind == "many nan" else max(1, n // 90), replace=False)] = float("nan")
+    got, cus = _topshare(gpu_lib, q, k, (n,), Hkv, bp)
+    with np.errstate(invalid="ignore"):
+        z = np.einsum("hgwd,hnd->hgwn", q.double().numpy()[0, 0].reshape(Hkv, G, W, d), k.double().numpy()[0])
+    ref = np.zeros((1, Hkv, n), np.float32)
+    for w in range(W):
+        seen = n - W + w + 1
+        kk = min(seen, max(1, seen * bp // 10000))
+        x = z[:, :, w, :seen]
+        order = np.sort(np.where(np.isnan(x), -np.inf if low else np.inf, x), axis=-1)[..., ::-1]
+        nan = np.isnan(x).sum(-1)
+        thr = order[..., kk - 1] if low else np.where(nan >= kk, np.nan, order[..., kk - 1])
+        if kk == seen:
+            thr = np.full_like(thr, -np.inf)
+        with np.errstate(invalid="ignore"):
+            ref[0, :, :seen] += (x >= thr[..., None]).sum(1)
+    np.testing.assert_array_equal(got, ref)
+
+
 def test_topshare_many_units(gpu_lib):
     """8,388,672 units of one row and two keys: more threads than one launch of
     some passes may hold.  Integer logits, so the larger one (both, if they tie)
