@@ -197,6 +197,11 @@ __global__ __launch_bounds__(TOPK_THREADS) void select_thresh_kernel(int B, int 
     // A head's logits (an entry past the row reads the last one), loaded
     // together.  Short rows hold every head's at once, issued ahead of the
     // barrier; longer ones take a head at a time (more in flight would spill).
+    // All ITEMS of the call's longest row are loaded whatever the row's own
+    // length (past it the same cached word): without branches the loads of a
+    // head are in flight together.  With the row's own items only, a batch of
+    // one 32K and 15 2K requests, 4 layers, 4 / 8 heads per KV head took 306 /
+    // 517 us against 288 / 477, one layer of 32K keys 48 against 42.
     constexpr bool HOLD = ITEMS * G <= 32;
     float x[HOLD ? G : 1][ITEMS];
     auto load = [&](int hh, float (&xx)[ITEMS]) {
