@@ -1,8 +1,10 @@
 """GPU parity of sg_score_topshare where its passes hand a row on: each sample
-size, intervals misjudged or widened by far outliers, bins of ties that reach
-the radix select, ranks at both ends, short requests beside long ones.  Inputs
-are integers, so every logit is exact in fp32 and fp64 and the counts must
-equal the oracle's."""
+size, intervals misjudged or widened by far outliers, bins of ties (one value,
+several side by side), lists that run over, ranks at both ends, logits that are
+not finite, short requests beside long ones, more units than a launch holds.
+Inputs are integers, so every logit is exact in fp32 and fp64 and the counts
+must equal the oracle's.  The calls' workspace shows which rows a path left to
+the radix select."""
 import numpy as np
 import pytest
 import torch
@@ -166,6 +168,35 @@ def test_topshare_ties_settle(gpu_lib, dtype, G, W, d, n, kind):
         ref = oracle.score_topshare(q.float().numpy(), k.float().numpy(), cus, Hkv, bp)
         np.testing.assert_array_equal(got, ref.astype(np.float32))
         assert sum(_radix_groups(ws, q, (n,), Hkv)) <= 1, bp      # (of up to 32 groups of rows)
+
+
+@pytest.mark.parametrize("dtype,G,W,d,n", [("bf16", 4, 64, 64, 8192), ("f32", 4, 16, 128, 3000), ("bf16", 8, 64, 128, 2500),
+                                           ("f32", 1, 33, 64, 14000)])
+def test_topshare_ties_side_by_side(gpu_lib, dtype, G, W, d, n):
+    """Three neighbouring logits with a twentieth of the keys each around the
+    threshold, the other keys far apart: where no bin tells them apart, the
+    radix select does."""
+    say("topshare ties side by side", dtype, G, W, d, n)
+    Hkv = 2
+    g = np.random.default_rng(n)
+    q = torch.zeros((1, 1, Hkv * G, W, d))
+    q[..., 0] = torch.from_numpy(g.integers(128, 257, q.shape[:-1]).astype(np.float32))
+    q[..., 1] = 1
+    k = torch.zeros((1, Hkv, n, d))
+    k[..., 0] = torch.from_numpy(g.integers(-250, 251, (1, Hkv, n)).astype(np.float32))
+    tied = torch.from_numpy(g.random((1, Hkv, n)) < 0.15)
+    k[..., 0] = torch.where(tied, 7.0, k[..., 0])
+    k[..., 1] = torch.from_numpy(g.integers(-1, 2, (1, Hkv, n)).astype(np.float32))
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    q, k = q.to(td), k.to(td)
+    left = 0
+    for bp in (4400, 4900, 5400):          # (41% of the keys lie above the ties)
+        ws = _workspace(gpu_lib, q, (n,), Hkv)
+        got, cus = _topshare(gpu_lib, q, k, (n,), Hkv, bp, ws=ws)
+        ref = oracle.score_topshare(q.float().numpy(), k.float().numpy(), cus, Hkv, bp)
+        np.testing.assert_array_equal(got, ref.astype(np.float32))
+        left += sum(_radix_groups(ws, q, (n,), Hkv))
+    assert left > 0
 
 
 @pytest.mark.parametrize("dtype,G,W,d,n,bp", [("bf16", 4, 16, 64, 3000, 2000), ("f32", 2, 33, 64, 1500, 300),
