@@ -125,11 +125,12 @@ __device__ __forceinline__ int64_t ts_rank(int64_t n, int ratio_bp) {
 
 // One workgroup of NWV wavefronts per (unit, ROWS rows): wavefront w holds the
 // logits of SPW sampled keys for those rows in registers, C = K Q^T, keys and
-// queries straight from memory.  The rows' intervals are narrowed by counting
-// the sample in 64 bins of the current interval (first [min, max]) and moving
-// its ends to the bins of the bounding ranks, again (up to four times) while
-// some row's interval holds many more samples than the ranks ask for (far
-// outliers; the larger sample always twice).  Also clears the unit's counters.
+// queries straight from memory; a row leaves out the samples past its causal
+// limit.  The rows' intervals are narrowed by counting the sample in 128 bins
+// of the current interval (first [min, max]) and moving its ends to the bins of
+// the bounding ranks, again (up to four times) while some row's interval holds
+// many more samples than the ranks ask for (far outliers; the larger sample
+// always twice).  Also clears the unit's counters.
 template <typename T, int D, int NWV, int ROWS>
 __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) void ts_sample_kernel(
     int B, int L, int Hq, int Hkv, int W, const int32_t *__restrict__ cu_seqlens, int64_t T_,
@@ -161,10 +162,13 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
     if (N < W) return;                         // uniform: the count pass writes zeros
     const T *qunit = q_win + (((int64_t)g.b * L + g.l) * Hq + (int64_t)g.h * (Hq / Hkv)) * W * D;
     const T *kunit = k + ((int64_t)g.l * k_layer_rows + (int64_t)g.h * T_ + g.s0) * D;
-    // ns keys of those every row sees (one in eight, at least 512: a short
-    // prompt beside long ones leaves wavefronts without keys, which only keep
-    // the barriers)
-    const int seen = N - W + 1, ns = min(seen, max(512, min(NS, seen / 8 / SPW * SPW)));
+    // ns of the keys (one in eight, at least 512: a short prompt beside long
+    // ones leaves wavefronts without keys, which only keep the barriers).  The
+    // window's own keys are among them, for the rows that see them: where they
+    // are the largest, in short prompts of rising logits, a sample of the keys
+    // that every row sees misjudges them all (200 keys, a window of 64: 8 layers
+    // 136 us against 83; 700 keys, a window of 512: 244 against 99).
+    const int seen = N - W + 1, ns = min(N, max(512, min(NS, N / 8 / SPW * SPW)));
     const bool busy = wave * SPW < ns;         // uniform across the wavefront
     TA<T, D> qf[NRB][M::KS];
 #pragma unroll
@@ -178,7 +182,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
             const int i = wave * SPW + kb * M::BM + lane % M::BM;
-            const T *p = kunit + (int64_t)sample_key(min(i, ns - 1), ns, seen) * D;
+            const T *p = kunit + (int64_t)sample_key(min(i, ns - 1), ns, N) * D;
             TA<T, D> kf[M::KS];
 #pragma unroll
             for (int ks = 0; ks < M::KS; ++ks) kf[ks] = M::load_global(p, ks, lane);
@@ -186,17 +190,27 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
             for (int rb = 0; rb < NRB; ++rb) val[kb][rb] = block_mma<T, D, true>(kf, qf[rb]);
         }
     }
-    // a short prompt's values past the sample become NaN, which every compare
-    // and minimum below leaves out
-    if (busy && ns % SPW != 0) {               // uniform
+    // values past a row's causal limit or past the sample (a short prompt)
+    // become NaN, which every compare and minimum below leaves out; samples
+    // below `early` have keys that every row sees
+    const float per = (float)ns / (float)N;
+    const int early = (int)((float)seen * per) - 1;
+    if (busy && (wave + 1) * SPW > early) {    // uniform
 #pragma unroll
-        for (int kb = 0; kb < NKB; ++kb)
+        for (int kb = 0; kb < NKB; ++kb) {
+            const int i0 = wave * SPW + kb * M::BM, i = i0 + lane % M::BM;
+            if (i0 + M::BM <= early) continue;
+            const int key = i < ns ? sample_key(i, ns, N) : N;
 #pragma unroll
             for (int v = 0; v < M::NV; ++v) {
-                const bool live = wave * SPW + kb * M::BM + M::crow(v, lane) < ns;
+                const int kv = __shfl(key, M::crow(v, lane), 64);
 #pragma unroll
-                for (int rb = 0; rb < NRB; ++rb) val[kb][rb][v] = live ? val[kb][rb][v] : __builtin_nanf("");
+                for (int rb = 0; rb < NRB; ++rb) {
+                    const int last = N - W + (grp * ROWS + rb * M::BM + lane % M::BM) % W;
+                    val[kb][rb][v] = kv <= last ? val[kb][rb][v] : __builtin_nanf("");
+                }
             }
+        }
     }
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
@@ -231,20 +245,18 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
         b = fmaxf(b, smax[w][col]);
     }
     const float top = b, quarter_range = 0.25f * (b - a);
-    // The row's newest keys, which not every row sees, are not sampled: its
-    // rank among the others lies between `r_least` (all of those above it) and
-    // `r_most` (none).  (200 keys, 63 of them the newest rows' own, of rising
-    // logits: with the rank's share alone every unit took hist again, 8 layers
-    // 135 us; 88 now.)
-    const int64_t nrow = seen + (grp * ROWS + col) % W, kk = ts_rank(nrow, ratio_bp);
-    const float per = (float)ns / (float)seen, p = (float)kk / (float)nrow;
-    const float r_most = (float)min(kk, (int64_t)seen) * per, r_least = (float)max(kk - (nrow - seen), (int64_t)0) * per;
+    // the row's keys and, of them, the sampled ones: those of whole stretches
+    // and, by its place, the one of the stretch that its last key is in
+    const int nrow = seen + (grp * ROWS + col) % W, whole = min((int)((float)nrow * per), ns);
+    const int srow = whole + (whole < ns && sample_key(whole, ns, N) < nrow ? 1 : 0);
+    const int64_t kk = ts_rank(nrow, ratio_bp);
+    const float p = (float)kk / (float)nrow, r = p * srow;
     // five standard deviations less a little; near the ends the wanted key lies inside the
-    // sample's extremes unless all the expected samples beyond it are missing
-    // (e^-11 from eleven on), else the interval is open there (r_hi < 0, r_lo > ns)
-    const float spread = 4.75f * sqrtf(p * ns * (1.f - p)) + 1.f;
-    const int r_hi = max((int)floorf(r_least - spread), r_least >= 11.f ? 0 : -1);
-    const int r_lo = min((int)ceilf(r_most + spread), (float)ns - r_most >= 11.f ? ns : ns + 1);
+    // sample's extremes unless all `r` expected samples beyond it are missing
+    // (e^-11 from r = 11 on), else the interval is open there (r_hi < 0, r_lo > srow)
+    const float spread = 4.75f * sqrtf(r * (1.f - p)) + 1.f;
+    const int r_hi = max((int)floorf(r - spread), r >= 11.f ? 0 : -1);
+    const int r_lo = min((int)ceilf(r + spread), (float)srow - r >= 11.f ? srow : srow + 1);
     for (int round = 0; round < 4; ++round) {
         const float sc = b > a ? (float)SB / (b - a) : 0.f;
         if (tid < ROWS) {
@@ -310,7 +322,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
             a = na;
             b = nb;
         }
-        const int want = min(r_lo, ns) - max(r_hi, 0);
+        const int want = min(r_lo, srow) - max(r_hi, 0);
         const int wide = grp * ROWS + col < R && found[3][col] - found[2][col] > want + want / 2 + 8;
         if (__syncthreads_or(wide) == 0 && round >= (NS > 512 ? 1 : 0)) break;     // uniform
     }
@@ -323,7 +335,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
         // 209 and 211)
         if (r_hi < 0) b = top + fmaxf(top - a, quarter_range);
         else if (b >= top) b = top + 1e-3f * (top - a);
-        if (r_lo > ns) a -= fmaxf(b - a, quarter_range);
+        if (r_lo > srow) a -= fmaxf(b - a, quarter_range);
         if (!(b > a)) {                        // a constant sample
             const float e = fmaxf(fabsf(a) * 1e-5f, 1e-20f);
             a -= e;

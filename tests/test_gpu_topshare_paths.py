@@ -90,13 +90,13 @@ def test_topshare_sample_is_fair(gpu_lib, n, kind):
     assert _radix_groups(ws, q, (n,), Hkv) == [0] * Hkv
 
 
-@pytest.mark.parametrize("W,n", [(64, 130), (64, 200), (64, 300), (64, 513), (33, 90)])
+@pytest.mark.parametrize("W,n", [(64, 130), (64, 200), (64, 300), (64, 513), (33, 90), (512, 700), (512, 513)])
 def test_topshare_window_keys_on_top(gpu_lib, W, n):
-    """Short prompts of rising logits: the window's own keys, which the sample
-    leaves out, are the largest, and the first histogram still holds every
-    row's threshold."""
+    """Short prompts of rising logits: the window's own keys, which only some
+    rows see, are the largest, and the first histogram holds every row's
+    threshold."""
     say("topshare window keys on top", W, n)
-    G, d, Hkv = 4, 64, 2
+    G, d, Hkv = 4 if W < 128 else 1, 64, 2
     q = _ints((1, 1, Hkv * G, W, d), 10, 50, n, "bf16")
     k = _ints((1, Hkv, n, d), -40, 40, n + 1, "bf16")
     k += torch.from_numpy((np.arange(n) * 200 // n).astype(np.float32)).to(torch.bfloat16)[None, None, :, None]
@@ -147,7 +147,8 @@ def test_topshare_ranks_at_the_ends(gpu_lib, dtype, n, kind, bp):
 
 @pytest.mark.parametrize("dtype,G,W,d,n,kind", [
     ("bf16", 4, 64, 64, 8192, "zeros"), ("bf16", 4, 64, 128, 5000, "few"), ("f32", 4, 16, 64, 3000, "few"),
-    ("bf16", 8, 64, 64, 4096, "few"), ("bf16", 2, 64, 64, 8192, "period 16"), ("bf16", 4, 32, 128, 8191, "period 64"),
+    ("bf16", 8, 64, 64, 4096, "few"), ("bf16", 4, 64, 64, 30000, "few"), ("f32", 2, 64, 64, 15000, "few"), ("bf16", 4, 64, 64, 5000, "large"),
+    ("f32", 4, 32, 128, 14000, "large"), ("bf16", 2, 64, 128, 30000, "large"), ("bf16", 2, 64, 64, 8192, "period 16"), ("bf16", 4, 32, 128, 8191, "period 64"),
     ("f32", 2, 33, 128, 4000, "period 16"), ("bf16", 1, 40, 64, 30000, "period 64"), ("bf16", 4, 64, 64, 9001, "half")])
 def test_topshare_ties_settle(gpu_lib, dtype, G, W, d, n, kind):
     """More equal logits at a row's threshold than it may gather (one value, a
@@ -160,6 +161,11 @@ def test_topshare_ties_settle(gpu_lib, dtype, G, W, d, n, kind):
         k *= -0.0
     elif kind == "half":
         k[:, :, ::2] = 0
+    elif kind == "large":         # two values, their step far below their size
+        g = np.random.default_rng(n)
+        q[..., 1:], k[..., 1:] = 0, 0
+        q[..., 0], k[..., 0], q[..., 1] = q[..., 0].abs() + 200, 255, 1
+        k[..., 1] = torch.from_numpy((g.random((1, Hkv, n)) < 0.3).astype(np.float32))
     elif kind != "few":
         k = k[:, :, torch.arange(n) % int(kind.split()[1])].contiguous()
     for bp in (700, 5000):
