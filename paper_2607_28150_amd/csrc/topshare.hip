@@ -323,7 +323,10 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
             b = nb;
         }
         const int want = min(r_lo, srow) - max(r_hi, 0);
-        const int wide = grp * ROWS + col < R && found[3][col] - found[2][col] > want + want / 2 + 8;
+        // (ties are not told apart, and an interval much narrower than its ends
+        // are large could not place its values)
+        const int wide = grp * ROWS + col < R && kk < nrow && b - a > 0x1p-11f * fmaxf(fabsf(a), fabsf(b)) &&
+                         found[3][col] - found[2][col] > want + want / 2 + 8;
         if (__syncthreads_or(wide) == 0 && round >= (NS > 512 ? 1 : 0)) break;     // uniform
     }
     if (owner) {
@@ -336,11 +339,17 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
         if (r_hi < 0) b = top + fmaxf(top - a, quarter_range);
         else if (b >= top) b = top + 1e-3f * (top - a);
         if (r_lo > srow) a -= fmaxf(b - a, quarter_range);
-        if (!(b > a)) {                        // a constant sample
-            const float e = fmaxf(fabsf(a) * 1e-5f, 1e-20f);
-            a -= e;
-            b += e;
+        // ties, a constant sample: no narrower than places every value to a
+        // fraction of a bin with an offset in fp32 (ties fell outside: 4 layers
+        // of 64K keys, logits of a few values, 3.03 ms, 0.86 now)
+        const float tight = fmaxf(0x1p-12f * fmaxf(fabsf(a), fabsf(b)), 2e-20f);
+        if (!(b - a >= tight)) {
+            a -= 0.5f * tight;
+            b += 0.5f * tight;
         }
+        const float edge = 1e-3f * (b - a);    // (a tied value at an end stays inside)
+        a -= edge;
+        b += edge;
         const float scale = 1.f / (b - a), off = 1.f - a * scale;
         const bool ok = b > a && scale < INFINITY && scale > 0.f && fabsf(off) < INFINITY;
         ws.xa[u * R + myrow] = ok ? scale : 0.f;           // 0, 0: every logit below the interval
@@ -533,7 +542,10 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
             xa = key_value(ts_bound(TS_LOW + 1 + bin, scale, off));
             xb = bin < TS_BINS ? key_value(ts_bound(TS_LOW + 2 + bin, scale, off) - 1u) : INFINITY;
         }
-        if (found && in_bin <= (uint32_t)TS_CMAX) {
+        if (found && bin < TS_BINS && xa == xb) {          // one value: nothing to gather
+            thr = xb;
+            xa = xb = INFINITY;
+        } else if (found && in_bin <= (uint32_t)TS_CMAX) {
             need = (uint32_t)rest | in_bin << 16;
         } else {
             // another interval: the bin, or (the sample misjudged the row) the
@@ -541,8 +553,11 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
             const float a = (1.f - off) / scale, w = 1.f / scale;
             const float up = above_in <= 4 * TS_CMAX ? 16.f * w : w;
             const float down = below <= 4 * TS_CMAX ? 16.f * w : w;
-            const float na = found ? xa - (xb - xa) * 1e-3f : inside ? a - down : a + w;
-            const float nb = found ? xb + (xb - xa) * 1e-3f : inside ? a : a + w + up;
+            // (the margins cover the rounding of the offset: a tied value at the
+            // first interval's end had fallen outside of both)
+            const float wide = fmaxf(xb - xa, 0x1p-18f * fmaxf(fabsf(xa), fabsf(xb)));
+            const float na = found ? xa - 0.02f * wide : inside ? a - down : a + 0.98f * w;
+            const float nb = found ? xb + 0.02f * wide : inside ? a + 0.02f * w : a + w + up;
             const float ns = 1.f / (nb - na), no = 1.f - na * ns;
             if (!AGAIN && nb > na && ns > 0.f && ns < INFINITY && fabsf(no) < INFINITY) {
                 need = TS_AGAIN;

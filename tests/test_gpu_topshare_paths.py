@@ -176,6 +176,28 @@ def test_topshare_ties_settle(gpu_lib, dtype, G, W, d, n, kind):
         assert sum(_radix_groups(ws, q, (n,), Hkv)) <= 1, bp      # (of up to 32 groups of rows)
 
 
+def test_topshare_tied_value_at_an_interval_end(gpu_lib):
+    """8,192 rows over 64K keys with logits of a few values: a row here and there
+    has its tied threshold at an end of its interval, and none loses it."""
+    say("topshare tied interval end")
+    L, Hkv, G, W, d, n, bp = 4, 8, 4, 64, 128, 65536, 2000
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    for shape in ((1, L, Hkv * G, W, d), (L, Hkv, n, d)):       # (draws of this seed with such a row)
+        torch.randn(shape, generator=gen, device="cuda", dtype=torch.bfloat16)
+    q, k = (torch.randint(-1, 2, shape, generator=gen, device="cuda").to(torch.bfloat16)
+            for shape in ((1, L, Hkv * G, W, d), (L, Hkv, n, d)))
+    ws = _workspace(gpu_lib, q, (n,), Hkv)
+    got, _ = _topshare(gpu_lib, q, k, (n,), Hkv, bp, ws=ws)
+    assert sum(_radix_groups(ws, q, (n,), Hkv)) == 0
+    pos = n - W + torch.arange(G * W, device="cuda") % W
+    for l, h in ((0, 0), (3, 6), (3, 7)):
+        z = q[0, l, h * G:(h + 1) * G].reshape(G * W, d).float() @ k[l, h].float().t().contiguous()
+        z.masked_fill_(torch.arange(n, device="cuda")[None] > pos[:, None], -1e9)
+        kth = (pos + 1) * bp // 10000
+        thr = z.sort(dim=1, descending=True).values.gather(1, (kth - 1)[:, None])
+        np.testing.assert_array_equal(got[l, h], (z >= thr).sum(0).float().cpu().numpy())
+
+
 @pytest.mark.parametrize("dtype,G,W,d,n", [("bf16", 4, 64, 64, 8192), ("f32", 4, 16, 128, 3000), ("bf16", 8, 64, 128, 2500),
                                            ("f32", 1, 33, 64, 14000)])
 def test_topshare_ties_side_by_side(gpu_lib, dtype, G, W, d, n):
