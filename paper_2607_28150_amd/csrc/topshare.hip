@@ -57,7 +57,6 @@ namespace sg {
 
 constexpr int TS_BINS = 64;        // bins of a row's interval
 constexpr int TS_CMAX = 92;        // keys a row may gather
-constexpr int TS_LIST = 32;        // of them in LDS, per chunk
 constexpr int TS_ROW_WORDS = 99;   // workspace words per row: six below, the rest bins, then lists
 constexpr int TS_UNIT_WORDS = 9;
 static_assert(6 + TS_CMAX <= TS_ROW_WORDS && TS_BINS <= TS_CMAX, "the row lists take the bins' place");
@@ -586,6 +585,13 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
 
 // ---------------------------------------------------------------- gather
 
+// The entries of a row's list in LDS, shared evenly by its lanes: 40 where two
+// workgroups per CU still hold them beside the tiles, else 32.  (A list that
+// runs over takes its workgroup's chunk once more: with 32 entries a call of
+// 256 units in a few had one, 290 us for the pass instead of 200.)
+template <typename T, int D, int NW>
+constexpr int ts_list() { return D * (int)sizeof(T) == 256 && NW < 8 ? 40 : 32; }
+
 // One block of the gather pass: the values of a row that lie in [xa, xb] are
 // appended to the lane's list in LDS (a row's values sit in the lanes of equal
 // lane % BM; each keeps its own).  Vector instructions only: the median of
@@ -601,7 +607,7 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
 template <typename T, int D, int NW, bool MASK, bool CARE = false>
 struct GatherStep {
     using M = MT<T, D>;
-    static constexpr int NRB = QFrags<T, D>::NRB, CAP = TS_LIST * M::BM / 64;   // entries per lane and row block
+    static constexpr int NRB = QFrags<T, D>::NRB, CAP = ts_list<T, D, NW>() * M::BM / 64;   // entries per lane and row block
     uint32_t *mylist;               // LDS, this lane's: [NRB][CAP], words 64 apart
     uint32_t (&cnt)[NRB];           // values gathered so far
     const float (&xa)[NRB], (&xb)[NRB];
