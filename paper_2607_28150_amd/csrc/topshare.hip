@@ -585,12 +585,13 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
 
 // ---------------------------------------------------------------- gather
 
-// The entries of a row's list in LDS, shared evenly by its lanes: 40 where two
-// workgroups per CU still hold them beside the tiles, else 32.  (A list that
-// runs over takes its workgroup's chunk once more: with 32 entries a call of
-// 256 units in a few had one, 290 us for the pass instead of 200.)
+// The entries of a row's list in LDS, shared evenly by its lanes: 40 where that
+// takes no workgroup off a CU (256 rows of 256 bytes a key), else 32.  A list
+// that runs over takes its workgroup's chunk once more: with 32 entries random
+// logits of 256 units did so now and then, 290 us for the pass instead of 200.
+// (At 64 and 128 rows, three workgroups per CU instead of four: 154 -> 168 us.)
 template <typename T, int D, int NW>
-constexpr int ts_list() { return D * (int)sizeof(T) == 256 && NW < 8 ? 40 : 32; }
+constexpr int ts_list() { return D * (int)sizeof(T) == 256 && NW == 4 ? 40 : 32; }
 
 // One block of the gather pass: the values of a row that lie in [xa, xb] are
 // appended to the lane's list in LDS (a row's values sit in the lanes of equal
