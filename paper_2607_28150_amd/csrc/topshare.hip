@@ -470,16 +470,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 
 constexpr int TS_DIGIT_THREADS = 64;
 
-// The order key of the smallest float (in bit-pattern order) that falls into
-// bin `d` of the interval or above it.
-__device__ __forceinline__ uint32_t ts_bound(int d, float scale, float off) {
-    uint32_t lo = 0x007fffffu, hi = 0xff800000u;       // order keys of -inf and +inf; +inf is above
-    while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo) / 2u;
-        if (ts_bin(key_value(mid), scale, off) >= d) hi = mid;
-        else lo = mid + 1u;
+// The order keys of the smallest float (in bit-pattern order) that falls into
+// bin `d` of the interval or above it, and into bin d + 1 or above.
+__device__ __forceinline__ void ts_bounds(int d, float scale, float off, uint32_t &k0, uint32_t &k1) {
+    constexpr uint32_t FIRST = 0x007fffffu, LAST = 0xff800000u;    // order keys of -inf and +inf; +inf is above
+    uint32_t lo0 = FIRST, hi0 = LAST, lo1 = FIRST, hi1 = LAST;
+    while (lo0 < hi0 || lo1 < hi1) {
+        const uint32_t m0 = lo0 + (hi0 - lo0) / 2u, m1 = lo1 + (hi1 - lo1) / 2u;
+        const bool at0 = ts_bin(key_value(m0), scale, off) >= d, at1 = ts_bin(key_value(m1), scale, off) > d;
+        hi0 = at0 ? m0 : hi0;
+        lo0 = at0 ? lo0 : min(m0 + 1u, hi0);
+        hi1 = at1 ? m1 : hi1;
+        lo1 = at1 ? lo1 : min(m1 + 1u, hi1);
     }
-    return lo;
+    k0 = lo0;
+    k1 = lo1;
 }
 
 // One thread per row, one workgroup per unit: the bin of the row's k-th
@@ -537,9 +542,11 @@ __global__ __launch_bounds__(TS_DIGIT_THREADS) void ts_digit_kernel(int R, int W
             rest = kk - above;
             in_bin = (uint32_t)below;
         }
-        if (found) {
-            xa = key_value(ts_bound(TS_LOW + 1 + bin, scale, off));
-            xb = bin < TS_BINS ? key_value(ts_bound(TS_LOW + 2 + bin, scale, off) - 1u) : INFINITY;
+        if (found) {                           // (both searches at once: their steps overlap)
+            uint32_t k0, k1;
+            ts_bounds(TS_LOW + 1 + bin, scale, off, k0, k1);
+            xa = key_value(k0);
+            xb = bin < TS_BINS ? key_value(k1 - 1u) : INFINITY;
         }
         if (found && bin < TS_BINS && xa == xb) {          // one value: nothing to gather
             thr = xb;
