@@ -157,8 +157,8 @@ int sg_score_count(void *stream, sg_dtype dt, int B, int L, int Hq, int Hkv, int
  *
  * so a row picks its k_w largest logits and every key tied with the k_w-th
  * (the threshold is exact: a histogram of the fp32 logits around it, finished
- * by ranking the few values left in a row's bin, or by a radix select where
- * they tie; the decisions are taken in
+ * by ranking the few values left in a row's bin, by the one value they share, or
+ * by a radix select where several tie; the decisions are taken in
  * fp32 on the raw products q . k_j, whose order the positive scale keeps; -0
  * equals +0).  Counts are integers in [0, G * W] stored as float, as in
  * sg_score_count.

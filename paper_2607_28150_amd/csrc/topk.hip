@@ -10,9 +10,9 @@
 // select region runs a request pair's top-k beside the next pair's score.
 //
 // Against four fixed 8-bit digit passes with consecutive keys per thread (512
-// threads for many long rows): 256 rows of 8K keys 14.5 -> 8.7 us, 1,024 rows
-// of 3K to 32K keys 179 -> 48 us, one row of 32K block importances 41.7 ->
-// 17.4 us (5.5 us of it its loads: what one CU draws from beyond its L2).
+// threads for many long rows): 256 rows of 8K keys 14.5 -> 8.6 us, 1,024 rows
+// of 2K to 32K keys 179 -> 41 us, one row of 32K block importances 41.7 ->
+// 16.2 us (5.5 us of it its loads: what one CU draws from beyond its L2).
 #include "select_common.h"
 
 namespace sg {

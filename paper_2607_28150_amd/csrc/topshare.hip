@@ -14,12 +14,14 @@
 //   sample : the logits of 512 to 2048 keys spread over the prompt (held in
 //            registers) give each row an interval [a, b) that holds its k-th
 //            largest logit with near certainty: the sample's quantiles 4.75
-//            standard deviations around the wanted rank;
+//            standard deviations around the wanted rank, or open ends with
+//            a quarter of the sample's range to spare;
 //   hist   : every logit of the row goes to one of 64 equal bins of [a, b), or
 //            below or above it (LDS atomics, bins x rows); the chunk's bins go
 //            into the unit's global histogram with integer atomics;
-//   digit  : one thread per row finds the bin of the k-th largest and the
-//            smallest and largest float in it;
+//   digit  : one thread per row finds the bin of the k-th largest (the keys
+//            above or below the interval are one too, if few) and the smallest
+//            and largest float in it;
 //   again  : units with a row that the sample misjudged or whose bin holds more
 //            than TS_CMAX keys take hist and digit once more, over the next
 //            interval or that bin (every other unit returns at once);
@@ -36,11 +38,11 @@
 // Against a radix select in 6-bit digits for all rows (three histogram passes,
 // gather and count, one workgroup per CU in each): 32 layers x 8 heads of 8K
 // keys, 256 rows each, at 20%: 1.14 -> 0.60-0.65 ms (sample 62, hist 187, digit
-// 13, gather 190, pick 25, count 137 us, the three idle launches 14 us); one
-// unit in ten or so has a row that takes hist again.  Rows of ties take hist
-// again and the plain loop of gather.  8 layers of 8K keys, every logit zero /
-// one of a few values / repeating every 64 keys: 0.32 / 0.33 / 0.48 ms; with the
-// radix select in gather's place 1.13 / 1.00 / 0.81, with one for all rows 0.63.
+// 13, gather 195, pick 25, count 139 us, the three idle launches 15 us).  Rows of
+// ties take hist again and the careful loop of gather.  8 layers of 8K keys,
+// every logit zero / one of a few values / repeating every 64 keys: 0.29 / 0.30
+// / 0.48 ms; with the radix select in gather's place 1.13 / 1.00 / 0.81, with one
+// for all rows 0.63.
 //
 // A logit's bits are the same in every pass: the same MFMA operands in the
 // same contraction order (C = K Q^T in hist and gather, Q K^T in count).  The
@@ -358,10 +360,11 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
 
 // ---------------------------------------------------------------- hist
 
-// Keys per LDS tile of the hist and gather passes: 64-key tiles leave room for
-// two workgroups per CU beside the bins or the lists.
-template <typename T>
-constexpr int ts_tile_keys() { return 64; }
+// Keys per LDS tile of the hist and gather passes: beside the bins or the
+// lists, 64-key tiles leave room for two workgroups per CU at rows of 256 bytes
+// a key up to four wavefronts and at 128 bytes always (fp32 at d = 128, and
+// eight wavefronts at 256 bytes: one).
+constexpr int TS_TILE_KEYS = 64;
 
 // One block of the histogram pass.  A word of the bins holds two rows' counts
 // (row blocks 2 i and 2 i + 1 of the wavefront, one after the other in a lane,
@@ -394,7 +397,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
     const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int nchunk, int chunk_keys,
     TsWork ws) {
     using M = MT<T, D>;
-    constexpr int TKEYS = ts_tile_keys<T>();
+    constexpr int TKEYS = TS_TILE_KEYS;
     using KT = KTile<T, D, TKEYS>;
     constexpr int NRB = QFrags<T, D>::NRB, WORDS = 32 * NW;
     __shared__ __attribute__((aligned(16))) char kbA[KT::BYTES];
@@ -686,7 +689,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
     const T *__restrict__ q_win, const T *__restrict__ k, int64_t k_layer_rows, int nchunk, int chunk_keys,
     TsWork ws) {
     using M = MT<T, D>;
-    constexpr int TKEYS = ts_tile_keys<T>();
+    constexpr int TKEYS = TS_TILE_KEYS;
     using KT = KTile<T, D, TKEYS>;
     constexpr int NRB = QFrags<T, D>::NRB;
     __shared__ __attribute__((aligned(16))) char kbA[KT::BYTES];

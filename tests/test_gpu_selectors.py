@@ -197,16 +197,16 @@ def _topshare(gpu_lib, q, k, lens, Hkv, ratio_bp, ws=None):
 
 @pytest.mark.parametrize("dtype,G,W,d,lens,bp,span", [
     ("f32", 4, 16, 64, (2500, 700), 2000, 3),        # two chunks, a second request, many ties
-    ("bf16", 4, 64, 64, (5000,), 2000, 3),           # 256 rows: 6-bit digits
+    ("bf16", 4, 64, 64, (5000,), 2000, 3),           # 256 rows
     ("bf16", 4, 64, 128, (3000, 1111), 2000, 40),    # d = 128, few ties
-    ("bf16", 8, 64, 64, (64, 3000), 2000, 3),        # 512 rows (5-bit digits); N = W
+    ("bf16", 8, 64, 64, (64, 3000), 2000, 3),        # 512 rows; N = W
     ("bf16", 8, 64, 64, (2345,), 700, 40),
     ("bf16", 1, 32, 64, (4100,), 1, 3),              # k = 1: each row's maxima
     ("bf16", 2, 64, 64, (3000, 1500), 10000, 3),     # k = n: every visible key
     ("f32", 8, 16, 64, (1300,), 5000, 40),           # 128 rows
     ("bf16", 4, 20, 64, (2222, 999), 333, 3),        # 80 rows: padded wavefront rows
     ("f32", 2, 8, 128, (777, 130), 2000, 3),         # a single wavefront, short prompts
-    ("f32", 8, 64, 128, (700,), 2000, 40),           # fp32 at 512 rows (8 wavefronts, 5-bit digits)
+    ("f32", 8, 64, 128, (700,), 2000, 40),           # fp32 at 512 rows (8 wavefronts)
     ("f32", 8, 64, 64, (1100, 64), 1500, 3),
 ])
 def test_score_topshare_exact(gpu_lib, dtype, G, W, d, lens, bp, span):
@@ -227,8 +227,8 @@ def test_score_topshare_mixed_rows(gpu_lib):
     """One unit whose rows take both ways to their threshold: keys in {-1, 0, 1};
     window rows w < 32 with queries in [-40, 40] see a few keys per logit value
     (their last bins are gathered and ranked), rows w >= 32 with queries in
-    {-1, 0, 1} see dozens of keys tied at every value (their bins stay too large
-    to gather and the radix passes go on).  Integer logits: exact."""
+    {-1, 0, 1} see dozens of keys tied at every value (gathered like the others, or
+    settled as ties where there are too many).  Integer logits: exact."""
     G, W, d, L, Hkv, lens = 4, 64, 64, 2, 2, (3000, 2100)
     say("score topshare mixed rows", lens)
     T = sum(lens)
